@@ -175,6 +175,9 @@ pd_status pd_schedule_multistep_tables(const pd_schedule* s, float* R, float* S)
  * scale per tile of 16 pixels and layer, and three part products per
  * multiply-add leave an error of about one float32 rounding.  A conv1x1 weight of magnitude 65504 or more makes creation fail
  * with PD_ERR_UNSUPPORTED; non-finite activations propagate as in float32.
+ * For the MLP a layer of 512 or more inputs runs in the same way, each weight
+ * scaled by a power of two per output feature and each input by one per row
+ * (finite weights of any magnitude), and a shorter one on the fp32 matrix cores.
  * dtype PD_BF16 (conv1x1 only) rounds every matmul operand to bfloat16
  * (round to nearest even) and accumulates in float32.
  * The training schedule `train` supplies abar (GMM) and T_train (the range
@@ -217,9 +220,9 @@ pd_status pd_denoiser_forward(const pd_denoiser* d, const float* x, const int32_
  * cannot allocate or synchronise anything (code under HIP graph capture,
  * tight serving loops, harnesses that forbid allocation): no allocation, no
  * event or lock; the launches on `stream` are all it does.  The MLP's hidden
- * activations (2 * width floats per row) go to a static device array of
- * 2^20 floats (4 MiB) that each GPU holds until the process ends, so for the
- * MLP M * 2 * width <= 2^20 (M <= 512 at width 1024); larger M returns
+ * activations (2 * width floats per row, and their row maxima) go to a static
+ * device array (8.5 MiB) that each GPU holds until the process ends, with room
+ * for 2^20 activations, so for the MLP M * 2 * width <= 2^20 (M <= 512 at width 1024); larger M returns
  * PD_ERR_INVALID_ARG.  The mixture and conv1x1 models use no scratch and take
  * any M.  Every call on one GPU shares that array: calls whose work overlaps
  * on the device (other streams, or host threads) race and give undefined

@@ -1,128 +1,382 @@
 // One output tile of a dense layer y = act(x W^T + bias) (or + shift[n_row]
-// for the first layer, which carries b1 + e_n) of the synthetic MLP denoiser,
-// on fp32 MFMA.  Shared by the layer kernel (mlp.hip) and the fused last
-// layer and Picard update (picard.hip), so both compute bitwise the same
-// epsilon.
+// for the first layer, which carries b1 + e_n) of the synthetic MLP denoiser.
+// Shared by the layer kernels (mlp.hip) and the fused last layer and Picard
+// update (picard.hip).
 //
-// v_mfma_f32_16x16x4f32 operand layout (wave64): A[i][k] sits in lane
-// i + 16 k, B[k][j] in lane j + 16 k, and D[i][j] in lane j + 16 (i / 4),
-// register i % 4.  Each lane loads four consecutive k of its row of x and of
-// W as one float4; step q of the four MFMAs then pairs element q of both
-// vectors, i.e. lane group h = lane / 16 covers k = k0 + 4 h + q.  Any
-// permutation of k works as long as A and B agree, so the loads stay
-// contiguous.
+// Layers are computed transposed, out^T = W x^T: the MFMA's M dimension is the
+// output feature and its N dimension the row.  A tile is RT x CT blocks of
+// 16 rows x 16 features; the block's kLinWaves waves each take a contiguous
+// run of the 32-input reduction chunks of the whole tile, so every weight and
+// input of the tile is loaded once per block, and the partial tiles are added
+// through LDS in wave order (the same order for every tile shape: a row's
+// result does not depend on how many rows there are).
 //
-// A tile is 16 rows x (16 kNSub) columns.  The block's kLinWaves waves split
-// K into contiguous runs of 16-wide chunks; each wave multiplies its x chunk
-// against kNSub column groups of W (the x operand is loaded once for all of
-// them), and the partial tiles are summed through LDS in wave order.
+// What bounds it: at the policy's sizes a layer is a few microseconds of
+// latency (launch, first loads, reduction) around the tile's loads, which one
+// compute unit takes in at 64 B a cycle.  So operands lie in memory exactly as
+// the lanes take them: lane l = i + 16 g of a chunk c holds inputs
+// k = 32 c + 16 q + 4 g + e (q = 0, 1; e = 0..3) of feature or row i,
+//   weights  [feature tile][c][q or part][lane][16 B]
+//   hidden   [row tile][k / 4][row][4]     (k / 4 = 8 c + 4 q + g)
+// and a wave's load is 1 KB (weights) or four runs of 256 B (rows), all of
+// them in flight before anything is waited for.  An accumulator holds, in lane
+// j + 16 g and register e, feature 4 g + e of row j: the hidden layout's own
+// four floats, so the next layer reads what this one stores.
+// On one MI355X a forward of the 160-1024-1024-1024-160 policy network over 777
+// rows went from 140 to 58 us, over 320 from 72 to 40, over 100 from 34 to 26 and
+// over one from 21.5 to 19.5 (row-major operands on fp32 MFMA before).
+//
+// Split products (SPLIT): a weight of feature n is held as 2^wexp[n] (w0 +
+// 2^-11 w1), two fp16 parts with the row's largest weight in [1, 2); an input
+// row x as x S = x0s + x1 in fp16 with S the power of two that puts the row's
+// largest value in [2^14, 2^15), and x0 = 2^-11 x0s.  w0 x0s + w0 x1 + w1 x0
+// then keeps about 22 bits of every product, and every fp16 product is exact
+// in the MFMA's fp32 accumulator: against float64 a forward of the policy is
+// 3.3e-7 off, 4.0e-7 with fp32 MFMA, at a fifth of the matrix time.  The row's
+// largest value comes from the producing layer, one maximum per row and
+// 16-feature tile (rmax); the first layer takes it from its own loads.  Layers
+// with few inputs and models with a non-finite weight run on fp32 MFMA.
 #pragma once
 
 #include "pd_internal.h"
 
 namespace pd {
 
-#ifndef PD_LIN_WAVES
-#define PD_LIN_WAVES 8
-#endif
-#ifndef PD_LIN_NSUB
-#define PD_LIN_NSUB 1
-#endif
-constexpr int kLinWaves = PD_LIN_WAVES;   // waves per block, splitting K
-constexpr int kNSub = PD_LIN_NSUB;        // 16-column groups per block
-constexpr int kLinBatch = 8;              // chunks whose loads are in flight together
-static_assert(kLinWaves * 64 >= 256 * kNSub, "every output of the tile needs a thread");
+constexpr int kLinWaves = 8;              // waves per block, splitting the reduction
+constexpr int kLinThreads = kLinWaves * 64;
 
+// GELU(u) = u Phi(u) = max(u, 0) - |u| Q(|u|), Q(t) = erfc(t / sqrt 2) / 2 =
+// exp(-t^2 / 2) G(t), with G (a scaled erfcx, smooth and slowly falling) as 1/2
+// and a polynomial of degree 8 in w = 0.29 t / (1 + 0.29 t): least squares
+// reweighted towards the largest relative error, 3.1e-8 on [0, 6].  One
+// reciprocal, one exponential and no branch, where u (1 + erff(u / sqrt 2)) / 2
+// took both of erff's branches.  Distance to float64 over normal u of
+// deviation 0.3, 1 and 3: 4.0e-8, 2.9e-8 and 2.2e-8, and with erff 4.1e-8, 3.9e-8 and 3.0e-8.
+// +inf gives inf, -inf and NaN give NaN (as the product with 1 + erf does).
 __device__ __forceinline__ float gelu_exact(float u) {
-    return 0.5f * u * (1.0f + erff(u / 1.41421356237f));
+    const float t = __builtin_fabsf(u > 30.f ? 30.f : u);
+    const float w = t * 0.29f * __builtin_amdgcn_rcpf(__builtin_fmaf(t, 0.29f, 1.0f));
+    float g = 0.0398590082f;
+    g = __builtin_fmaf(g, w, -0.123180827f);
+    g = __builtin_fmaf(g, w, 0.0589313836f);
+    g = __builtin_fmaf(g, w, 0.160809925f);
+    g = __builtin_fmaf(g, w, 0.0255656515f);
+    g = __builtin_fmaf(g, w, -0.883300482f);
+    g = __builtin_fmaf(g, w, 1.59700807f);
+    g = __builtin_fmaf(g, w, -1.37566304f);
+    g = __builtin_fmaf(g, w, 0.5f);
+    const float e = __builtin_amdgcn_exp2f(t * t * -0.72134752f);   // log2(e) / 2
+    return __builtin_fmaf(-t, e * g, u > 0.f ? u : 0.f);
 }
 
-// Rows of the layer's input: gathered from the window's ring slots (GATHER,
-// the first layer) or a dense [M][K] buffer.  M rows are valid; the tile
-// starts at row m0 < M and column n0.  Every thread of the block calls it.
-template <bool GATHER>
-__device__ __forceinline__ void linear_tile(const LinearArgs& a, const float* __restrict__ xd,
-                                            const RowSrc& src, int64_t D, float* __restrict__ y,
-                                            int M, int m0, int n0) {
-    typedef float f4 __attribute__((ext_vector_type(4)));
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int li = lane & 15, h = lane >> 4;
-    const int K = a.K, N = a.N;
+// Barrier for LDS traffic only: global loads and stores issued before it may
+// still be in flight.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
 
-    // row pointer of this lane's A row (clamped rows are computed, not stored)
-    const int mr = min(m0 + li, M - 1);
-    const float* xrow;
-    if (GATHER) {
-        const int g = mr / src.group, b = mr % src.group;
-        const int64_t sl = src.slot ? src.slot[g] : g;
-        xrow = src.base + sl * src.slot_stride + (int64_t)b * D;
-    } else {
-        xrow = xd + (int64_t)mr * K;
+typedef float lin_f4 __attribute__((ext_vector_type(4)));
+typedef _Float16 lin_h8 __attribute__((ext_vector_type(8)));
+typedef uint32_t lin_u4 __attribute__((ext_vector_type(4)));
+
+// Row tile mt of a hidden buffer of M rows: rows of the tile (the last tile is
+// stored without padding).
+__device__ __forceinline__ int tile_rows(int M, int mt) { return min(16, M - 16 * mt); }
+// First float of row (16 mt + j)'s run in a hidden buffer of width K; input k
+// sits at + (k / 4) tile_rows * 4 + k % 4
+__device__ __forceinline__ int64_t hidden_row(int K, int mt, int j) { return (int64_t)mt * 16 * K + 4 * j; }
+// Word of the maximum of row j of row tile mt over feature tile nt (NT of
+// them): [mt][nt / 4][row][nt % 4]
+__device__ __forceinline__ int64_t rmax_word(int NT, int mt, int rows, int nt, int j) {
+    return (int64_t)mt * 16 * ((NT + 3) / 4 * 4) + ((int64_t)(nt >> 2) * rows + j) * 4 + (nt & 3);
+}
+
+__device__ __forceinline__ uint32_t umax32(uint32_t a, uint32_t b) { return a > b ? a : b; }
+
+// LDS of a tile.  The maxima are bits of |x| (unsigned order: NaN above inf
+// above every number).
+template <int RT, int CT>
+struct LinearLds {
+    float part[kLinWaves][RT * CT][256];
+    uint32_t mx[kLinWaves][16 * RT];
+    float inv[16 * RT];                    // 1 / S of the tile's rows
+    uint32_t pm[RT * CT][4][16];           // maxima of the tile's outputs, per 4 features
+};
+
+// One chunk's operands of a lane: inputs 16 q + 4 g + e of each row tile; the
+// two 16-byte halves (fp32) or parts (fp16) of each feature tile's weights.
+template <int RT, int CT>
+struct LinearChunk {
+    lin_f4 x[RT][2];
+    lin_f4 w[CT][2];
+};
+
+struct SplitX {
+    lin_h8 x0s, x1, x0;
+};
+__device__ __forceinline__ SplitX split_row(const lin_f4& a, const lin_f4& b, float S, bool nonfinite) {
+    lin_u4 p0, p1;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const float v0 = q < 2 ? a[2 * q] : b[2 * q - 4], v1 = q < 2 ? a[2 * q + 1] : b[2 * q - 3];
+        const float h0 = v0 * S, h1 = v1 * S;                 // exact: a power of two
+        uint32_t u, w;
+        float d0, d1;
+        asm("v_cvt_pk_f16_f32 %0, %1, %2" : "=v"(u) : "v"(h0), "v"(h1));
+        asm("v_fma_mix_f32 %0, %1, %2, -%3 op_sel_hi:[0,0,1]" : "=v"(d0) : "v"(v0), "v"(S), "v"(u));
+        asm("v_fma_mix_f32 %0, %1, %2, -%3 op_sel:[0,0,1] op_sel_hi:[0,0,1]" : "=v"(d1) : "v"(v1), "v"(S), "v"(u));
+        asm("v_cvt_pk_f16_f32 %0, %1, %2" : "=v"(w) : "v"(d0), "v"(d1));
+        p0[q] = u;
+        p1[q] = w;
     }
-    const float* wrow[kNSub];
+    SplitX s;
+    s.x0s = __builtin_bit_cast(lin_h8, p0);
+    s.x1 = __builtin_bit_cast(lin_h8, p1);
+    s.x0 = s.x0s * (_Float16)0.00048828125f;
+    if (nonfinite) {
+        // an infinite or NaN input keeps its leading part only, so that its
+        // products are those of the value itself
 #pragma unroll
-    for (int s = 0; s < kNSub; ++s) wrow[s] = a.W + (int64_t)min(n0 + 16 * s + li, N - 1) * K;
+        for (int i = 0; i < 8; ++i) {
+            const uint32_t bits = (p0[i >> 1] >> (16 * (i & 1))) & 0x7fff;
+            if (bits >= 0x7c00) s.x1[i] = s.x0[i] = (_Float16)0.f;
+        }
+    }
+    return s;
+}
 
-    // epilogue: thread tid owns output (row m0 + 4 (l / 16) + q, column
-    // n0 + 16 s + l % 16) with l = tid % 64, q = (tid / 64) % 4, s = tid / 256
-    // (threads past 64 * 4 * kNSub own none); its bias or per-timestep shift
-    // is fetched before the products so the latency hides behind them
-    const int el = threadIdx.x & 63, eq = (threadIdx.x >> 6) & 3, es = threadIdx.x >> 8;
-    const bool owner = es < kNSub;
-    const int em = m0 + 4 * (el >> 4) + eq, en = n0 + 16 * es + (el & 15);
-    float addv = 0.f;
-    if (owner) {
-        const int mc = min(em, M - 1), nc = min(en, N - 1);
-        addv = a.shift != nullptr ? a.shift[(int64_t)row_timestep(src, mc / src.group) * N + nc] : a.bias[nc];
+// The tile of row tiles mt0.. and feature tiles nt0..; every thread of the
+// block calls it, and emit(tile, u) is then called for the block's outputs: u
+// the pre-activation of row j = (tid / 4) % 16 and feature 4 g + e, g =
+// (tid / 64) % 4, e = tid % 4, of the 16 x 16 block (row tile mt0 + tile / CT,
+// feature tile nt0 + tile % CT), which is the same for the whole wave (the row
+// or feature may lie past the end: nothing is stored for those).  Returns false, with
+// nothing emitted, when no row of the tile is active.  Input rows: gathered
+// from the window's ring slots or a [rows][D] batch (GATHER), else a hidden
+// buffer of the launch's largest row count.  Rows and inputs past the end are
+// clamped (to the last active row where rows are gathered, else to the last
+// row of the buffer), loaded and count for nothing.
+template <int RT, int CT, bool GATHER, bool SPLIT, class Emit>
+__device__ __forceinline__ bool linear_tile(const LinearArgs& a, const RowSrc& src, const HiddenBuf& in,
+                                            int64_t D, int mt0, int nt0, LinearLds<RT, CT>& lds, Emit&& emit) {
+    static_assert(RT == 1 || RT == 2, "the row maxima are shared out over 512 threads");
+    typedef LinearChunk<RT, CT> Chunk;
+    const int tid = threadIdx.x, lane = tid & 63, j = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int groups = src.active ? *src.active : src.max_groups;
+    const int Mmax = src.max_groups * src.group;
+    const int K = a.K, N = a.N, K4 = K / 4;
+    const int KC = (K + 31) / 32, NT = (N + 15) / 16;
+    // gathered rows need the loop state first: only the active groups' slots
+    // are set (past them a slot may never have been written)
+    if constexpr (GATHER) {
+        if (16 * mt0 >= groups * src.group) return false;     // uniform over the block
+    }
+    const int Mread = GATHER ? groups * src.group : Mmax;
+
+    // the input rows' largest values, read first (loads return in order)
+    uint32_t mrow = 0;
+    if constexpr (SPLIT && !GATHER) {
+        constexpr int PARTS = kLinThreads / (16 * RT);
+        const int r = tid % (16 * RT), part = tid / (16 * RT);
+        const int row = min(16 * mt0 + r, Mmax - 1), mt = row >> 4;
+        const int NTi = (K + 15) / 16, rows = tile_rows(Mmax, mt);
+        for (int n4 = part; n4 < (NTi + 3) / 4; n4 += PARTS) {
+            const lin_u4 v = *reinterpret_cast<const lin_u4*>(in.rmax + rmax_word(NTi, mt, rows, 4 * n4, row & 15));
+#pragma unroll
+            for (int e = 0; e < 4; ++e) mrow = umax32(mrow, 4 * n4 + e < NTi ? v[e] : 0u);
+        }
     }
 
-    // this wave's chunks: a contiguous run of 16-wide k chunks
-    const int nchunks = (K + 15) / 16;
-    const int per = (nchunks + kLinWaves - 1) / kLinWaves;
-    const int c_begin = w * per, c_end = min(c_begin + per, nchunks);
-    f4 acc[kNSub];
+    // this lane's row of each row tile
+    const float* xp[RT];
+    int xs[RT];                                   // floats from one input group of four to the next
 #pragma unroll
-    for (int s = 0; s < kNSub; ++s) acc[s] = f4{0.f, 0.f, 0.f, 0.f};
-    for (int c0 = c_begin; c0 < c_end; c0 += kLinBatch) {
-        f4 av[kLinBatch], bv[kLinBatch][kNSub];
+    for (int rt = 0; rt < RT; ++rt) {
+        const int row = min(16 * (mt0 + rt) + j, Mread - 1);
+        if constexpr (GATHER) {
+            const int gr = row / src.group, b = row % src.group;
+            const int64_t sl = src.slot ? src.slot[gr] : gr;
+            xp[rt] = src.base + sl * src.slot_stride + (int64_t)b * D;
+            xs[rt] = 4;
+        } else {
+            const int mt = row >> 4;
+            xp[rt] = in.h + hidden_row(K, mt, row & 15);
+            xs[rt] = 4 * tile_rows(Mmax, mt);
+        }
+    }
+    const lin_f4* wp[CT];
 #pragma unroll
-        for (int u = 0; u < kLinBatch; ++u) {
-            const int k = (c0 + u) * 16 + 4 * h;
-            const bool ok = c0 + u < c_end && k < K;   // K is a multiple of 4
-            const int kk = ok ? k : 0;
-            const f4 xa = *reinterpret_cast<const f4*>(xrow + kk);
-            av[u] = ok ? xa : f4{0.f, 0.f, 0.f, 0.f};
+    for (int ct = 0; ct < CT; ++ct)
+        wp[ct] = static_cast<const lin_f4*>(a.w) + (int64_t)min(nt0 + ct, NT - 1) * KC * 128 + lane;
+
+    const int per = (KC + kLinWaves - 1) / kLinWaves;
+    const int c_begin = wave * per, c_end = min(c_begin + per, KC);
+    auto load = [&](int c) -> Chunk {
+        Chunk ch;
+        c = min(c, KC - 1);
 #pragma unroll
-            for (int s = 0; s < kNSub; ++s) {
-                const f4 wb = *reinterpret_cast<const f4*>(wrow[s] + kk);
-                bv[u][s] = ok ? wb : f4{0.f, 0.f, 0.f, 0.f};
+        for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+            for (int q = 0; q < 2; ++q) ch.w[ct][q] = wp[ct][(int64_t)c * 128 + q * 64];
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const int k4 = min(8 * c + 4 * q + g, K4 - 1);
+                ch.x[rt][q] = *reinterpret_cast<const lin_f4*>(xp[rt] + (int64_t)k4 * xs[rt]);
             }
+        return ch;
+    };
+
+    // U chunks at a time, in two register sets: at 1024 inputs the small tiles
+    // have all four chunks of a wave in flight at once
+    constexpr int U = RT + CT <= 3 ? 2 : 1;
+    Chunk A[U], B[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) A[u] = load(c_begin + u);
+#pragma unroll
+    for (int u = 0; u < U; ++u) B[u] = load(c_begin + U + u);
+
+    // epilogue operands, fetched before the products
+    constexpr int E = (RT * CT * 256 + kLinThreads - 1) / kLinThreads;   // outputs per thread
+    float addv[E], wsv[E];
+    // the 16 x 16 block of a thread's i-th output is the same for its whole
+    // wave: kept in scalar registers, with all addresses that follow from it
+    const int upper = __builtin_amdgcn_readfirstlane(tid >> 8);
+    const int o = tid & 255, oj = (o >> 2) & 15, on = 4 * (o >> 6) + (o & 3);
+#pragma unroll
+    for (int i = 0; i < E; ++i) {
+        const int tile = min(2 * i + upper, RT * CT - 1);
+        const int n = min(16 * (nt0 + tile % CT) + on, N - 1);
+        const int row = min(16 * (mt0 + tile / CT) + oj, Mread - 1);
+        addv[i] = GATHER ? a.shift[(int64_t)row_timestep(src, src.group == 1 ? row : row / src.group) * N + n] : a.bias[n];
+        wsv[i] = SPLIT ? a.wscale[n] : 1.f;
+    }
+    // the loads above stay ahead of this exit (they need no loop state)
+    asm volatile("" ::: "memory");
+    if (16 * mt0 >= groups * src.group) return false;         // uniform over the block
+
+    float S[RT];
+    bool nonfinite = false;
+    if constexpr (SPLIT) {
+        if constexpr (GATHER) {
+            // this wave's chunks of each row, from the registers that hold the
+            // first ones (clamped inputs repeat one of the row)
+            uint32_t m[RT];
+            auto take = [&](const Chunk& ch) {
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                    for (int u = 0; u < 8; ++u)
+                        m[rt] = umax32(m[rt], __builtin_bit_cast(uint32_t, (float)ch.x[rt][u / 4][u % 4]) & 0x7fffffffu);
+            };
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) m[rt] = 0;
+#pragma unroll
+            for (int u = 0; u < U; ++u) take(A[u]);
+#pragma unroll
+            for (int u = 0; u < U; ++u) take(B[u]);
+            for (int c = c_begin + 2 * U; c < c_end; ++c) take(load(c));
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) {
+                m[rt] = umax32(m[rt], __shfl_xor(m[rt], 16, 64));
+                m[rt] = umax32(m[rt], __shfl_xor(m[rt], 32, 64));
+                if (g == 0) lds.mx[wave][16 * rt + j] = m[rt];
+            }
+        } else {
+            if constexpr (RT == 1) mrow = umax32(mrow, __shfl_xor(mrow, 16, 64));
+            mrow = umax32(mrow, __shfl_xor(mrow, 32, 64));
+            if (lane < 16 * RT) lds.mx[wave][lane] = mrow;
+        }
+        lds_barrier();
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+            uint32_t m = lds.mx[0][16 * rt + j];
+#pragma unroll
+            for (int v = 1; v < kLinWaves; ++v) m = umax32(m, lds.mx[v][16 * rt + j]);
+            // S = 2^(14 - e), e the exponent of the largest value; a zero row
+            // takes 1, and so does a row with a non-finite value
+            int e = 14;
+            if (m >= 0x7f800000u) nonfinite = true;
+            else if (m > 0) e = (int)(m >> 23) - 127;
+            e = e < -100 ? -100 : e;
+            S[rt] = __builtin_bit_cast(float, (uint32_t)(14 - e + 127) << 23);
+            // 1 / S = 2^(e - 14), normal for every e above
+            if (wave == 0 && g == 0) lds.inv[16 * rt + j] = __builtin_bit_cast(float, (uint32_t)(e - 14 + 127) << 23);
+        }
+        nonfinite = __ballot(nonfinite) != 0;
+    }
+
+    lin_f4 acc[RT][CT];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) acc[rt][ct] = lin_f4{0.f, 0.f, 0.f, 0.f};
+    auto compute = [&](Chunk& ch, int c) {
+        if (8 * c + 8 > K4) {                                 // inputs past K (the last chunk of a ragged K)
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+                if (8 * c + 4 * q + g >= K4)
+#pragma unroll
+                    for (int rt = 0; rt < RT; ++rt) ch.x[rt][q] = lin_f4{0.f, 0.f, 0.f, 0.f};
         }
 #pragma unroll
-        for (int u = 0; u < kLinBatch; ++u)
+        for (int rt = 0; rt < RT; ++rt) {
+            if constexpr (SPLIT) {
+                const SplitX s = split_row(ch.x[rt][0], ch.x[rt][1], S[rt], nonfinite);
 #pragma unroll
-            for (int s = 0; s < kNSub; ++s)
+                for (int p = 0; p < 3; ++p)
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    acc[s] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u][q], bv[u][s][q], acc[s], 0, 0, 0);
+                    for (int ct = 0; ct < CT; ++ct)
+                        acc[rt][ct] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                            __builtin_bit_cast(lin_h8, ch.w[ct][p == 2 ? 1 : 0]), p == 0 ? s.x0s : p == 1 ? s.x1 : s.x0,
+                            acc[rt][ct], 0, 0, 0);
+            } else {
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+#pragma unroll
+                    for (int ct = 0; ct < CT; ++ct)
+                        acc[rt][ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(ch.w[ct][u / 4][u % 4], ch.x[rt][u / 4][u % 4],
+                                                                           acc[rt][ct], 0, 0, 0);
+            }
+        }
+    };
+    for (int c = c_begin; c < c_end; c += 2 * U) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (c + u < c_end) compute(A[u], c + u);
+            if (c + 2 * U + u < c_end) A[u] = load(c + 2 * U + u);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (c + U + u < c_end) compute(B[u], c + U + u);
+            if (c + 3 * U + u < c_end) B[u] = load(c + 3 * U + u);
+        }
     }
 
-    // partial tiles, [wave][column group][register][lane]: conflict-free
-    // writes (one register of 64 lanes at a time) and reads (64 lanes)
-    __shared__ float s_acc[kLinWaves][kNSub][4][64];
+    // partial tiles, 1 KB per wave and 16 x 16 block: conflict-free 16-byte
+    // writes and 4-byte reads
 #pragma unroll
-    for (int s = 0; s < kNSub; ++s)
+    for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) s_acc[w][s][q][lane] = acc[s][q];
-    __syncthreads();
-    if (owner && em < M && en < N) {
-        float sum = s_acc[0][es][eq][el];
+        for (int ct = 0; ct < CT; ++ct)
+            *reinterpret_cast<lin_f4*>(&lds.part[wave][rt * CT + ct][4 * lane]) = acc[rt][ct];
+    lds_barrier();
 #pragma unroll
-        for (int v = 1; v < kLinWaves; ++v) sum += s_acc[v][es][eq][el];
-        float v = sum + addv;
-        if (a.act == ACT_GELU) v = gelu_exact(v);
-        y[(int64_t)em * N + en] = v;
+    for (int i = 0; i < E; ++i) {
+        const int tile = 2 * i + upper;
+        if (tile < RT * CT) {                                 // uniform over the wave
+            float sum = lds.part[0][tile][o];
+#pragma unroll
+            for (int v = 1; v < kLinWaves; ++v) sum += lds.part[v][tile][o];
+            const float u = SPLIT ? __builtin_fmaf(sum * lds.inv[16 * (tile / CT) + oj], wsv[i], addv[i]) : sum + addv[i];
+            emit(tile, u);
+        }
     }
+    return true;
 }
 
 }  // namespace pd

@@ -19,10 +19,10 @@ struct HeunPredictArgs {
     float* xt;             // [p][B * D] predictions
 };
 
-// The last layer of the MLP (dense input x, [rows][K]) into y, and each
-// output's Euler prediction into h.xt.  y and h.xt hold what
-// launch_linear_dense and the separate prediction kernel give, bit for bit.
-void launch_linear_dense_predict(const LinearArgs& a, const float* x, const RowSrc& rows,
-                                 const HeunPredictArgs& h, float* y, hipStream_t s);
+// The last layer of the MLP into y, and each output's Euler prediction into
+// h.xt.  y and h.xt hold what launch_linear_out and the separate prediction
+// kernel give, bit for bit.
+void launch_linear_out_predict(const LinearArgs& a, const HiddenBuf& in, const RowSrc& rows, const HeunPredictArgs& h,
+                               float* y, hipStream_t s);
 
 }  // namespace pd

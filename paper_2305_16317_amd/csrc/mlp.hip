@@ -1,86 +1,242 @@
-// Dense layer of the synthetic MLP denoiser on fp32 MFMA: one block per output
-// tile (the tile itself is computed in linear_tile.h).  At the policy
-// network's sizes (100 rows in a window, one in the sequential chain) the
-// layer is bound by latency and by the cost of dispatching waves, not by the
-// matrix core: few waves with a few dozen MFMAs each beat many waves with a
-// handful.
+// Dense layers of the synthetic MLP denoiser on the matrix cores: one block
+// per output tile (the tile itself is computed in linear_tile.h).  A layer is
+// bound by the loads of its busiest compute unit and by the latency around
+// them, so the launch picks the tile by the rows and features it has.
 #include "linear_tile.h"
 #include "mlp.h"
 
 namespace pd {
 namespace {
 
-template <bool GATHER>
-__global__ __launch_bounds__(kLinWaves * 64) void k_linear(LinearArgs a, const float* __restrict__ xd,
-                                                RowSrc src, int64_t D, float* __restrict__ y) {
-    const int groups = src.active ? *src.active : src.max_groups;
-    const int M = groups * src.group;
-    const int m0 = blockIdx.y * 16, n0 = blockIdx.x * (16 * kNSub);
-    if (m0 >= M) return;
-    linear_tile<GATHER>(a, xd, src, D, y, M, m0, n0);
-}
-
-// The last layer, then Heun's Euler prediction of each output the block
-// wrote: the thread that stored an output (the tile's epilogue mapping) reads
-// it back, so it sees its own store, and adds the drift
-// A_m x + B_m eps with two rounded products and a rounded sum, as the scan's
-// drift does.
-__global__ __launch_bounds__(kLinWaves * 64) void k_linear_predict(LinearArgs a,
-                                                                   const float* __restrict__ xd,
-                                                                   RowSrc src, HeunPredictArgs h,
-                                                                   float* y) {
-    const int groups = src.active ? *src.active : src.max_groups;
-    const int M = groups * src.group;
-    const int m0 = blockIdx.y * 16, n0 = blockIdx.x * (16 * kNSub);
-    if (m0 >= M) return;
-    linear_tile<false>(a, xd, src, 0, y, M, m0, n0);
-    const int el = threadIdx.x & 63, eq = (threadIdx.x >> 6) & 3, es = threadIdx.x >> 8;
-    const int em = m0 + 4 * (el >> 4) + eq, en = n0 + 16 * es + (el & 15);
-    if (es < kNSub && em < M && en < a.N) {
-        const LoopState cur = *h.st;
-        const int j = em / src.group, b = em % src.group;
-        const int m = cur.t + j;
-        const int64_t BD = (int64_t)src.group * a.N;
-        const int64_t c = (int64_t)b * a.N + en;
-        const float x = h.ring[(int64_t)((m <= cur.f ? m : cur.f) % h.ring_slots) * BD + c];
-        const float e = y[(int64_t)em * a.N + en];
-        const float dr = __fadd_rn(__fmul_rn(h.A[m], x), __fmul_rn(h.B[m], e));
-        h.xt[(int64_t)j * BD + c] = __fadd_rn(x, dr);
+// A hidden layer: GELU of the tile into the next layer's input layout, and the
+// maximum of each row over each 16-feature tile.
+template <int RT, int CT, bool GATHER, bool SPLIT>
+__global__ __launch_bounds__(kLinThreads) void k_linear(LinearArgs a, RowSrc src, HiddenBuf in, int64_t D,
+                                                        HiddenBuf out) {
+    __shared__ LinearLds<RT, CT> lds;
+    const int mt0 = blockIdx.y * RT, nt0 = blockIdx.x * CT;
+    const int Mmax = src.max_groups * src.group, N = a.N;
+    const int M = (src.active ? *src.active : src.max_groups) * src.group;
+    const int j = (threadIdx.x >> 2) & 15, g = (threadIdx.x >> 6) & 3, e = threadIdx.x & 3;
+    const bool any = linear_tile<RT, CT, GATHER, SPLIT>(
+        a, src, in, D, mt0, nt0, lds, [&](int tile, float u) {
+            const float v = gelu_exact(u);
+            const int mt = mt0 + tile / CT, nt = nt0 + tile % CT, rows = tile_rows(Mmax, mt);
+            const bool valid = j < M - 16 * mt && 4 * g + e < N - 16 * nt;
+            if (valid) (out.h + hidden_row(N, mt, 0) + (int64_t)nt * 16 * rows)[(g * rows + j) * 4 + e] = v;
+            // largest of the quad's four features
+            uint32_t m = valid ? __builtin_bit_cast(uint32_t, v) & 0x7fffffffu : 0u;
+            m = umax32(m, (uint32_t)__builtin_amdgcn_mov_dpp((int)m, 0xb1, 0xf, 0xf, false));
+            m = umax32(m, (uint32_t)__builtin_amdgcn_mov_dpp((int)m, 0x4e, 0xf, 0xf, false));
+            if (e == 0) lds.pm[tile][g][j] = m;
+        });
+    if (!any) return;
+    lds_barrier();
+    const int NT = (N + 15) / 16;
+    for (int i = threadIdx.x; i < RT * CT * 16; i += kLinThreads) {
+        const int tile = i >> 4, j = i & 15;
+        const int mt = mt0 + tile / CT, nt = nt0 + tile % CT;
+        if (16 * mt + j < M && nt < NT) {
+            const uint32_t m = umax32(umax32(lds.pm[tile][0][j], lds.pm[tile][1][j]),
+                                      umax32(lds.pm[tile][2][j], lds.pm[tile][3][j]));
+            out.rmax[rmax_word(NT, mt, tile_rows(Mmax, mt), nt, j)] = m;
+        }
     }
 }
 
+// The last layer: epsilon, row-major.  With h, each output's Euler prediction
+// follows (Heun's first stage): the drift A_m x + B_m eps with two rounded
+// products and a rounded sum, as the scan's drift does.
+template <int RT, int CT, bool SPLIT, bool PREDICT>
+__global__ __launch_bounds__(kLinThreads) void k_linear_out(LinearArgs a, RowSrc src, HiddenBuf in,
+                                                            HeunPredictArgs h, float* __restrict__ y) {
+    __shared__ LinearLds<RT, CT> lds;
+    const int mt0 = blockIdx.y * RT, nt0 = blockIdx.x * CT;
+    const int M = (src.active ? *src.active : src.max_groups) * src.group, N = a.N;
+    linear_tile<RT, CT, false, SPLIT>(
+        a, src, in, 0, mt0, nt0, lds, [&](int tile, float e) {
+            const int row = 16 * (mt0 + tile / CT) + ((threadIdx.x >> 2) & 15);
+            const int n = 16 * (nt0 + tile % CT) + 4 * ((threadIdx.x >> 6) & 3) + (threadIdx.x & 3);
+            if (row >= M || n >= N) return;
+            y[(int64_t)row * N + n] = e;
+            if constexpr (PREDICT) {
+                const LoopState cur = *h.st;
+                const int j = row / src.group, b = row % src.group;
+                const int m = cur.t + j;
+                const int64_t BD = (int64_t)src.group * N;
+                const int64_t c = (int64_t)b * N + n;
+                const float x = h.ring[(int64_t)((m <= cur.f ? m : cur.f) % h.ring_slots) * BD + c];
+                const float dr = __fadd_rn(__fmul_rn(h.A[m], x), __fmul_rn(h.B[m], e));
+                h.xt[(int64_t)j * BD + c] = __fadd_rn(x, dr);
+            }
+        });
+}
+
+// Weights [N][K] -> packed fragments (layout in linear_tile.h), one block per
+// 16 features; with `split`, also each feature's power of two.  *nonfinite is
+// set when a weight is infinite or NaN.
+__global__ __launch_bounds__(256) void k_pack_linear(const float* __restrict__ W, int N, int K, int split,
+                                                     float* __restrict__ out, float* __restrict__ wscale,
+                                                     int32_t* nonfinite) {
+    __shared__ uint32_t s_max[16];
+    const int nt = blockIdx.x, tid = threadIdx.x, i = tid & 15;
+    const int n = 16 * nt + i;
+    if (tid < 16) s_max[tid] = 0;
+    __syncthreads();
+    uint32_t m = 0;
+    for (int k = tid >> 4; n < N && k < K; k += 16)
+        m = umax32(m, __builtin_bit_cast(uint32_t, W[(int64_t)n * K + k]) & 0x7fffffffu);
+    atomicMax(&s_max[i], m);
+    __syncthreads();
+    m = s_max[i];
+    if (m >= 0x7f800000u) *nonfinite = 1;        // every writer stores the same value
+    int e = m > 0 && m < 0x7f800000u ? (int)(m >> 23) - 127 : 0;
+    e = e < -126 ? -126 : e;
+    // w 2^-e in [1, 2) for the feature's largest weight, in two exact steps
+    // (2^-e alone may exceed the float range)
+    const float f1 = __builtin_bit_cast(float, (uint32_t)(-(e / 2) + 127) << 23);
+    const float f2 = __builtin_bit_cast(float, (uint32_t)(-(e - e / 2) + 127) << 23);
+    if (split && tid < 16 && n < N) wscale[n] = __builtin_bit_cast(float, (uint32_t)(e + 127) << 23);
+    const int KC = (K + 31) / 32;
+    float* dst = out + (int64_t)nt * KC * 512;   // 2 KB per chunk
+    // thread: feature i, inputs 32 c + 16 (u / 4) + 4 g + u % 4 of lane i + 16 g
+    for (int q = tid >> 4; q < KC * 4; q += 16) {
+        const int c = q >> 2, g = q & 3, lane = i + 16 * g;
+        float w[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int k = 32 * c + 16 * (u / 4) + 4 * g + u % 4;
+            w[u] = n < N && k < K ? W[(int64_t)n * K + k] : 0.f;
+        }
+        if (split) {
+            lin_h8 p0, p1;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const float s = w[u] * f1 * f2;
+                p0[u] = (_Float16)s;
+                p1[u] = (_Float16)((s - (float)p0[u]) * 2048.f);
+            }
+            reinterpret_cast<lin_h8*>(dst)[(c * 2) * 64 + lane] = p0;
+            reinterpret_cast<lin_h8*>(dst)[(c * 2 + 1) * 64 + lane] = p1;
+        } else {
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                reinterpret_cast<lin_f4*>(dst)[(c * 2 + h) * 64 + lane] =
+                    lin_f4{w[4 * h], w[4 * h + 1], w[4 * h + 2], w[4 * h + 3]};
+        }
+    }
+}
+
+// The tile of a launch, in 16 x 16 blocks.  A block loads RT row tiles and CT
+// feature tiles whole (64 KB each at 1024 inputs), so the busiest compute unit
+// takes in rounds x (RT + CT) of them; ties go to the smaller tile (more
+// blocks, less to add up).  Four layers of 1024 (160 in and out), us: one row
+// 19.4 as 1 x 1 and 21.9 as 1 x 2; 100 rows 28.8, 26.3, 30.7 as 2 x 2; 160 rows
+// 35.5, 37.5, 31.1; 320 rows 49, 51, 41; 777 rows 97, 98, 60.  Larger tiles
+// (2 x 4, 4 x 4) have one block per unit, whose phases nothing overlaps: 64 and
+// 63 us at 777 rows.
+struct TileChoice {
+    int rt, ct;
+};
+TileChoice choose_tile(int64_t rows, int N) {
+    static constexpr TileChoice kTiles[] = {{1, 1}, {1, 2}, {2, 2}};
+    const int64_t MT = (rows + 15) / 16, NT = (N + 15) / 16, cus = device_cus();
+    TileChoice best{1, 1};
+    int64_t cost = INT64_MAX;
+    for (const TileChoice& t : kTiles) {
+        const int64_t blocks = ((MT + t.rt - 1) / t.rt) * ((NT + t.ct - 1) / t.ct);
+        const int64_t c = (blocks + cus - 1) / cus * (t.rt + t.ct);
+        if (c < cost) {
+            cost = c;
+            best = t;
+        }
+    }
+    return best;
+}
+
+// f(rows per tile, features per tile as integral constants, grid)
+template <class F>
+void with_tile(int64_t rows, int N, F&& f) {
+    const TileChoice t = choose_tile(rows, N);
+    auto go = [&](auto rt, auto ct) {
+        constexpr int RT = decltype(rt)::value, CT = decltype(ct)::value;
+        f(rt, ct, dim3((unsigned)((N + 16 * CT - 1) / (16 * CT)), (unsigned)((rows + 16 * RT - 1) / (16 * RT))));
+    };
+    using std::integral_constant;
+    if (t.rt == 2) go(integral_constant<int, 2>{}, integral_constant<int, 2>{});
+    else if (t.ct == 2) go(integral_constant<int, 1>{}, integral_constant<int, 2>{});
+    else go(integral_constant<int, 1>{}, integral_constant<int, 1>{});
+}
+
+void check_sizes(const LinearArgs& a) {
+    if ((a.K % 4) != 0 || (a.N % 4) != 0) fail(PD_ERR_UNSUPPORTED, "mlp layer sizes must be multiples of 4");
+}
+
 template <bool GATHER>
-void launch(const LinearArgs& a, const float* xd, const RowSrc& src, int64_t D, float* y,
-            hipStream_t s) {
-    const int64_t Mmax = (int64_t)src.max_groups * src.group;
-    if (Mmax == 0) return;
-    if ((a.K % 4) != 0 || (GATHER && (D % 4) != 0))
-        fail(PD_ERR_UNSUPPORTED, "mlp layer sizes must be multiples of 4");
-    const dim3 grid((unsigned)((a.N + 16 * kNSub - 1) / (16 * kNSub)), (unsigned)((Mmax + 15) / 16));
-    hipLaunchKernelGGL(k_linear<GATHER>, grid, dim3(kLinWaves * 64), 0, s, a, xd, src, D, y);
+void launch_hidden(const LinearArgs& a, const RowSrc& rows, const HiddenBuf& in, int64_t D, const HiddenBuf& out,
+                   hipStream_t s) {
+    const int64_t M = (int64_t)rows.max_groups * rows.group;
+    if (M == 0) return;
+    check_sizes(a);
+    with_tile(M, a.N, [&](auto rt, auto ct, dim3 grid) {
+        constexpr int RT = decltype(rt)::value, CT = decltype(ct)::value;
+        const dim3 block(kLinThreads);
+        if (a.wscale) hipLaunchKernelGGL((k_linear<RT, CT, GATHER, true>), grid, block, 0, s, a, rows, in, D, out);
+        else hipLaunchKernelGGL((k_linear<RT, CT, GATHER, false>), grid, block, 0, s, a, rows, in, D, out);
+    });
+    PD_HIP(hipGetLastError());
+}
+
+template <bool PREDICT>
+void launch_out(const LinearArgs& a, const HiddenBuf& in, const RowSrc& rows, const HeunPredictArgs& h, float* y,
+                hipStream_t s) {
+    const int64_t M = (int64_t)rows.max_groups * rows.group;
+    if (M == 0) return;
+    check_sizes(a);
+    with_tile(M, a.N, [&](auto rt, auto ct, dim3 grid) {
+        constexpr int RT = decltype(rt)::value, CT = decltype(ct)::value;
+        const dim3 block(kLinThreads);
+        if (a.wscale) hipLaunchKernelGGL((k_linear_out<RT, CT, true, PREDICT>), grid, block, 0, s, a, rows, in, h, y);
+        else hipLaunchKernelGGL((k_linear_out<RT, CT, false, PREDICT>), grid, block, 0, s, a, rows, in, h, y);
+    });
     PD_HIP(hipGetLastError());
 }
 
 }  // namespace
 
-void launch_linear_gather(const LinearArgs& a, const RowSrc& src, int64_t D, float* y,
-                          hipStream_t s) {
-    launch<true>(a, nullptr, src, D, y, s);
+size_t hidden_floats(int64_t rows, int width) {
+    const int64_t nt4 = ((width + 15) / 16 + 3) / 4 * 4;
+    return (size_t)(rows * width + rows * nt4 + 3) / 4 * 4;
+}
+HiddenBuf hidden_buf(float* p, int64_t rows, int width) {
+    return HiddenBuf{p, reinterpret_cast<uint32_t*>(p + rows * width)};
 }
 
-void launch_linear_dense(const LinearArgs& a, const float* x, const RowSrc& rows, float* y,
-                         hipStream_t s) {
-    launch<false>(a, x, rows, 0, y, s);
-}
+size_t packed_linear_floats(int N, int K) { return (size_t)((N + 15) / 16) * ((K + 31) / 32) * 512; }
 
-void launch_linear_dense_predict(const LinearArgs& a, const float* x, const RowSrc& rows,
-                                 const HeunPredictArgs& h, float* y, hipStream_t s) {
-    const int64_t Mmax = (int64_t)rows.max_groups * rows.group;
-    if (Mmax == 0) return;
-    if ((a.K % 4) != 0) fail(PD_ERR_UNSUPPORTED, "mlp layer sizes must be multiples of 4");
-    const dim3 grid((unsigned)((a.N + 16 * kNSub - 1) / (16 * kNSub)), (unsigned)((Mmax + 15) / 16));
-    hipLaunchKernelGGL(k_linear_predict, grid, dim3(kLinWaves * 64), 0, s, a, x, rows, h, y);
+void launch_pack_linear(const float* W, int N, int K, float* out, float* wscale, int32_t* nonfinite,
+                        hipStream_t s) {
+    hipLaunchKernelGGL(k_pack_linear, dim3((unsigned)((N + 15) / 16)), dim3(256), 0, s, W, N, K, wscale ? 1 : 0, out,
+                       wscale, nonfinite);
     PD_HIP(hipGetLastError());
+}
+
+void launch_linear_first(const LinearArgs& a, const RowSrc& src, int64_t D, const HiddenBuf& out, hipStream_t s) {
+    launch_hidden<true>(a, src, HiddenBuf{}, D, out, s);
+}
+
+void launch_linear_hidden(const LinearArgs& a, const HiddenBuf& in, const RowSrc& rows, const HiddenBuf& out,
+                          hipStream_t s) {
+    launch_hidden<false>(a, rows, in, 0, out, s);
+}
+
+void launch_linear_out(const LinearArgs& a, const HiddenBuf& in, const RowSrc& rows, float* y, hipStream_t s) {
+    launch_out<false>(a, in, rows, HeunPredictArgs{}, y, s);
+}
+
+void launch_linear_out_predict(const LinearArgs& a, const HiddenBuf& in, const RowSrc& rows, const HeunPredictArgs& h,
+                               float* y, hipStream_t s) {
+    launch_out<true>(a, in, rows, h, y, s);
 }
 
 }  // namespace pd

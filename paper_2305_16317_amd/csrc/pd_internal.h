@@ -152,20 +152,35 @@ size_t gmm_loop_lds_bytes(int T, int K, int p, int batch);
 void launch_gmm_picard_loop(const GmmLoopArgs& a, size_t max_lds, hipStream_t s);
 void launch_gmm_sequential_loop(const GmmLoopArgs& a, hipStream_t s);
 
-// mlp.hip: y = act(x W^T + bias [+ shift[n_row]]) with fp32 MFMA.
-enum Act { ACT_NONE = 0, ACT_GELU = 1 };
+// mlp.hip: y = act(x W^T + bias [+ shift[n_row]]) on the matrix cores.
 struct LinearArgs {
-    const float* W;       // [N][K]
+    const void* w;        // packed weights (layout in linear_tile.h)
+    const float* wscale;  // [N] power of two of each feature's split weights, or
+                          // nullptr: fp32 weights
     const float* bias;    // [N] (ignored when shift != nullptr)
     const float* shift;   // [T_train][N] per-timestep shift, or nullptr
     int32_t K, N;
-    int32_t act;
 };
-// rows from `src` (gathered, first layer) or from a dense [M][K] buffer.
-void launch_linear_gather(const LinearArgs& a, const RowSrc& src, int64_t D, float* y,
+// A hidden layer's activations in the layout the next layer reads, and the
+// largest |value| (bits) of each row over each 16-feature tile.
+struct HiddenBuf {
+    float* h;
+    uint32_t* rmax;
+};
+size_t hidden_floats(int64_t rows, int width);           // floats of one buffer (a multiple of 4)
+HiddenBuf hidden_buf(float* p, int64_t rows, int width);
+size_t packed_linear_floats(int N, int K);
+// W [N][K] (device) -> out; split into fp16 parts when wscale is given.
+// *nonfinite (device) is set when a weight is infinite or NaN.
+void launch_pack_linear(const float* W, int N, int K, float* out, float* wscale, int32_t* nonfinite,
+                        hipStream_t s);
+// first layer (rows gathered from `src`, fp32 weights), a hidden layer, and the
+// last layer (no activation, row-major output).  Buffers are those of
+// max_groups * group rows.
+void launch_linear_first(const LinearArgs& a, const RowSrc& src, int64_t D, const HiddenBuf& out, hipStream_t s);
+void launch_linear_hidden(const LinearArgs& a, const HiddenBuf& in, const RowSrc& rows, const HiddenBuf& out,
                           hipStream_t s);
-void launch_linear_dense(const LinearArgs& a, const float* x, const RowSrc& rows, float* y,
-                         hipStream_t s);
+void launch_linear_out(const LinearArgs& a, const HiddenBuf& in, const RowSrc& rows, float* y, hipStream_t s);
 
 // conv.hip: per-pixel 4-layer stack with fp32 or bf16 MFMA.
 // The kernels take the argument of e^-u in base 2, t = kNegLog2e u, as their
@@ -246,7 +261,7 @@ void launch_picard_finalize(const FinalizeArgs& fin, hipStream_t s);
 // n_slabs + 1 ints, zero between launches.
 struct HeadScanArgs {
     LinearArgs l4;          // the last layer: W4 [D][W], b4, no activation
-    const float* h;         // [rows][W] the third layer's output
+    HiddenBuf h;            // the third layer's output
     RowSrc rows;            // the window's rows (the layer's row count)
     const LoopState* st;
     float* ring;

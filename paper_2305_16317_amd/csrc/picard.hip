@@ -100,14 +100,6 @@ __global__ __launch_bounds__(256) void k_heun_predict(const LoopState* __restric
 }
 
 
-// Barrier for LDS traffic only: global stores issued before it need not have
-// completed (later kernels read them, no wave of this block does).
-__device__ __forceinline__ void lds_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 // The stride is known: record it, slide the window and write the next
 // iteration's row descriptors.  cur is the loop state as the iteration found
 // it.  mt / mt2 (or nullptr: read the tables) hold model_t[t + i] /
@@ -270,8 +262,8 @@ __device__ bool count_in(int32_t* cnt, int n) {
 constexpr int kHeadRows = 4;                 // window rows per group
 static_assert(kHeadGroups * kHeadRows >= kMaxWindow, "the head covers every window size");
 
-template <bool NOISE>
-__global__ __launch_bounds__(kLinWaves * 64) void k_mlp_head_scan(HeadScanArgs a, FinalizeArgs fin) {
+template <bool NOISE, bool SPLIT>
+__global__ __launch_bounds__(kLinThreads) void k_mlp_head_scan(HeadScanArgs a, FinalizeArgs fin) {
     const LoopState cur = *a.st;
     const int pe = cur.p_eff;
     if (pe <= 0) return;
@@ -279,7 +271,13 @@ __global__ __launch_bounds__(kLinWaves * 64) void k_mlp_head_scan(HeadScanArgs a
     const int M = pe * B;                        // rows (window point, sample)
     const int slab = blockIdx.x, m0 = blockIdx.y * 16, n0 = slab * 16;
     if (m0 >= M) return;                         // uniform over the block
-    linear_tile<false>(a.l4, a.h, a.rows, 0, a.eps, M, m0, n0);
+    __shared__ LinearLds<1, 1> lds;
+    linear_tile<1, 1, false, SPLIT>(a.l4, a.rows, a.h, 0, blockIdx.y, slab, lds,
+                                    [&](int, float e) {
+                                        const int row = m0 + ((threadIdx.x >> 2) & 15);
+                                        const int n = n0 + 4 * ((threadIdx.x >> 6) & 3) + (threadIdx.x & 3);
+                                        if (row < M && n < a.D) a.eps[(int64_t)row * a.D + n] = e;
+                                    });
 
     // the slab's last block rebuilds its columns from every block's epsilon
     if (!count_in(&a.count[slab], (M + 15) / 16)) return;
@@ -756,11 +754,12 @@ void launch_mlp_head_scan(const HeadScanArgs& a, const FinalizeArgs& fin, hipStr
     if ((a.l4.K % 4) != 0) fail(PD_ERR_UNSUPPORTED, "mlp layer sizes must be multiples of 4");
     if (a.n_slabs != (int)((a.D + 15) / 16) || fin.history || fin.nrow2)
         fail(PD_ERR_INVALID_ARG, "fused head: slab count or drift kind mismatch");
-    const dim3 grid((unsigned)a.n_slabs, (unsigned)(((int64_t)fin.p * a.batch + 15) / 16));
-    if (a.noise)
-        hipLaunchKernelGGL(k_mlp_head_scan<true>, grid, dim3(kLinWaves * 64), 0, s, a, fin);
-    else
-        hipLaunchKernelGGL(k_mlp_head_scan<false>, grid, dim3(kLinWaves * 64), 0, s, a, fin);
+    const dim3 grid((unsigned)a.n_slabs, (unsigned)(((int64_t)fin.p * a.batch + 15) / 16)), block(kLinThreads);
+    const bool split = a.l4.wscale != nullptr;
+    if (a.noise && split) hipLaunchKernelGGL((k_mlp_head_scan<true, true>), grid, block, 0, s, a, fin);
+    else if (a.noise) hipLaunchKernelGGL((k_mlp_head_scan<true, false>), grid, block, 0, s, a, fin);
+    else if (split) hipLaunchKernelGGL((k_mlp_head_scan<false, true>), grid, block, 0, s, a, fin);
+    else hipLaunchKernelGGL((k_mlp_head_scan<false, false>), grid, block, 0, s, a, fin);
     PD_HIP(hipGetLastError());
 }
 

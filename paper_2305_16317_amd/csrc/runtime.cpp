@@ -341,8 +341,8 @@ struct pd_denoiser {
     int C = 0, T_train = 0, device = 0;
     // gmm2d
     DevBuf means, g_a, g_inv2s2, g_coef;
-    // mlp
-    DevBuf W[4], bias[4], shift1;
+    // mlp: packed weights, and the powers of two of the split ones
+    DevBuf W[4], bias[4], shift1, wscale[4];
     // conv1x1
     DevBuf frags, shift_u, shift_c;
     // pd_denoiser_forward's MLP scratch (kForwardRows rows).  Calls may come
@@ -363,28 +363,26 @@ struct pd_denoiser {
                          desc.n_components};
     }
 
+    // floats of the two hidden buffers of an MLP forward
     size_t scratch_floats(int64_t rows) const {
-        return desc.kind == PD_MODEL_MLP ? (size_t)(2 * rows * desc.width) : 0;
+        return desc.kind == PD_MODEL_MLP ? 2 * hidden_floats(rows, desc.width) : 0;
     }
 
-    // MLP: the first three layers through scratch (2 * rows * width floats);
-    // returns the third layer's output, the last layer's input
-    const float* mlp_trunk(const RowSrc& src, float* scratch, hipStream_t s) const {
+    LinearArgs mlp_layer(int i) const {
         const int Wd = desc.width;
-        const int64_t rows = (int64_t)src.max_groups * src.group;
-        float* h1 = scratch;
-        float* h2 = scratch + rows * Wd;
-        LinearArgs l1{W[0].as<float>(), nullptr, shift1.as<float>(), (int)D, Wd, ACT_GELU};
-        LinearArgs l2{W[1].as<float>(), bias[1].as<float>(), nullptr, Wd, Wd, ACT_GELU};
-        LinearArgs l3{W[2].as<float>(), bias[2].as<float>(), nullptr, Wd, Wd, ACT_GELU};
-        launch_linear_gather(l1, src, D, h1, s);
-        launch_linear_dense(l2, h1, src, h2, s);
-        launch_linear_dense(l3, h2, src, h1, s);
-        return h1;
+        return LinearArgs{W[i].p, wscale[i].as<float>(), bias[i].as<float>(), i == 0 ? shift1.as<float>() : nullptr,
+                          i == 0 ? (int)D : Wd, i == 3 ? (int)D : Wd};
     }
-    // MLP: the last layer (no activation)
-    LinearArgs mlp_head() const {
-        return LinearArgs{W[3].as<float>(), bias[3].as<float>(), nullptr, desc.width, (int)D, ACT_NONE};
+    // MLP: the first three layers through scratch (scratch_floats of the
+    // largest row count); returns the third layer's output, the last layer's input
+    HiddenBuf mlp_trunk(const RowSrc& src, float* scratch, hipStream_t s) const {
+        const int64_t rows = (int64_t)src.max_groups * src.group;
+        const HiddenBuf h1 = hidden_buf(scratch, rows, desc.width);
+        const HiddenBuf h2 = hidden_buf(scratch + hidden_floats(rows, desc.width), rows, desc.width);
+        launch_linear_first(mlp_layer(0), src, D, h1, s);
+        launch_linear_hidden(mlp_layer(1), h1, src, h2, s);
+        launch_linear_hidden(mlp_layer(2), h2, src, h1, s);
+        return h1;
     }
 
     void forward(const RowSrc& src, float* eps, float* scratch, hipStream_t s) const {
@@ -393,7 +391,7 @@ struct pd_denoiser {
                 launch_gmm_eps(gmm(), src, eps, s);
                 break;
             case PD_MODEL_MLP:
-                launch_linear_dense(mlp_head(), mlp_trunk(src, scratch, s), src, eps, s);
+                launch_linear_out(mlp_layer(3), mlp_trunk(src, scratch, s), src, eps, s);
                 break;
             case PD_MODEL_CONV1X1: {
                 ConvArgs a{frags.p,           shift_u.as<float>(),
@@ -410,6 +408,39 @@ struct pd_denoiser {
         }
     }
 };
+
+// Packed weights of the MLP's four layers, laid out on the device.  A layer of
+// kSplitInputs inputs or more is split into fp16 parts: there the split's own
+// rounding (half a unit of fp32 per operand) is less than what fp32 sums of that
+// length lose.  Error of a forward against float64, all layers split and all
+// on fp32 MFMA: 3.4e-7 and 4.2e-7 at width 1024, 2.9e-7 and 3.1e-7 at 512,
+// 2.6e-7 and 2.4e-7 at 256.  With an infinite or NaN weight the whole model
+// keeps fp32 weights, whose products propagate those as they are.
+static constexpr int kSplitInputs = 512;
+static void pack_mlp(pd_denoiser& d, const float* W1, const float* W2, const float* W3, const float* W4) {
+    const int Wd = d.desc.width, Din = (int)d.D;
+    const float* w[4] = {W1, W2, W3, W4};
+    const int n[4] = {Wd, Wd, Wd, Din}, k[4] = {Din, Wd, Wd, Wd};
+    DevBuf raw[4], flag;
+    const int32_t zero = 0;
+    flag.upload(&zero, 1);
+    for (int i = 0; i < 4; ++i) {
+        raw[i].upload(w[i], (size_t)n[i] * k[i]);
+        d.W[i].alloc(packed_linear_floats(n[i], k[i]) * sizeof(float));
+        if (k[i] >= kSplitInputs) d.wscale[i].alloc(sizeof(float) * (size_t)n[i]);
+        launch_pack_linear(raw[i].as<float>(), n[i], k[i], d.W[i].as<float>(), d.wscale[i].as<float>(),
+                           flag.as<int32_t>(), nullptr);
+    }
+    int32_t nonfinite = 0;
+    PD_HIP(hipMemcpy(&nonfinite, flag.p, sizeof nonfinite, hipMemcpyDeviceToHost));
+    if (!nonfinite) return;
+    for (int i = 0; i < 4; ++i) {
+        if (!d.wscale[i].p) continue;
+        d.wscale[i].alloc(0);
+        launch_pack_linear(raw[i].as<float>(), n[i], k[i], d.W[i].as<float>(), nullptr, flag.as<int32_t>(), nullptr);
+    }
+    PD_HIP(hipStreamSynchronize(nullptr));     // raw is freed on return
+}
 
 static void create_denoiser(const pd_model_desc& m, const int64_t* shape, int32_t ndim,
                             const float* const* w, int32_t nw, const pd_schedule& train,
@@ -480,10 +511,7 @@ static void create_denoiser(const pd_model_desc& m, const int64_t* shape, int32_
     d.bias[2].upload(w[5], Wd);
     d.bias[3].upload(w[7], (size_t)Din);
     if (m.kind == PD_MODEL_MLP) {
-        d.W[0].upload(W1, (size_t)Wd * Din);
-        d.W[1].upload(W2, (size_t)Wd * Wd);
-        d.W[2].upload(W3, (size_t)Wd * Wd);
-        d.W[3].upload(W4, (size_t)Din * Wd);
+        pack_mlp(d, W1, W2, W3, W4);
         d.shift1.upload(sh.data(), sh.size());
         d.fwd_scratch.alloc(d.scratch_floats(kForwardRows) * sizeof(float));
         PD_HIP(hipEventCreateWithFlags(&d.fwd_done, hipEventDisableTiming));
@@ -577,8 +605,10 @@ extern "C" pd_status pd_denoiser_forward(const pd_denoiser* d, const float* x,
 // Each GPU holds its own copy until the process ends.  In host code the name
 // stands for a host-side symbol, not a device address: kernels get the
 // address hipGetSymbolAddress returns for the current device.
-static constexpr size_t kStaticScratchFloats = (size_t)1 << 20;   // 4 MiB
-static __device__ __align__(256) float scratch[kStaticScratchFloats];
+// Rows are limited by the activations alone (2 * width floats a row); the array
+// also holds their row maxima, at most width / 16 + 4 words a row and buffer.
+static constexpr size_t kStaticScratchFloats = (size_t)1 << 20;
+static __device__ __align__(256) float scratch[2 * kStaticScratchFloats + (kStaticScratchFloats >> 3)];   // 8.5 MiB
 
 namespace {
 constexpr int kMaxDevices = 64;
@@ -606,13 +636,14 @@ extern "C" pd_status pd_denoiser_forward_static(const pd_denoiser* d, const floa
     return guard([&] {
         require(d != nullptr, "denoiser must not be NULL");
         require(M >= 0 && M <= (int64_t)1 << 30, "M out of range");
-        const size_t need = d->scratch_floats(M);
+        const size_t per_row = d->desc.kind == PD_MODEL_MLP ? 2 * (size_t)d->desc.width : 0;
+        const size_t need = per_row * (size_t)M;
         if (need > kStaticScratchFloats)
             fail(PD_ERR_INVALID_ARG,
                  "M = " + std::to_string(M) + " needs " + std::to_string(need) +
                      " floats of scratch; the static scratch holds " +
                      std::to_string(kStaticScratchFloats) + " (M <= " +
-                     std::to_string(kStaticScratchFloats / d->scratch_floats(1)) +
+                     std::to_string(kStaticScratchFloats / per_row) +
                      " at this width)");
         if (M == 0) return;
         require(x && model_t && eps, "NULL device pointer");
@@ -1016,9 +1047,9 @@ extern "C" pd_status pd_sample_picard(const pd_schedule* s, const pd_denoiser* d
                     if (it == need - 1) PD_HIP(hipEventRecord(w.batch_event, st));
                     if (head) {
                         // the last layer with the update, error, stride and slide
-                        const float* h = d->mlp_trunk(src, w.scratch.as<float>(), st);
+                        const HiddenBuf h = d->mlp_trunk(src, w.scratch.as<float>(), st);
                         tm.mark(CAT_DENOISER);
-                        const HeadScanArgs ha{d->mlp_head(), h, src, dst, w.ring.as<float>(),
+                        const HeadScanArgs ha{d->mlp_layer(3), h, src, dst, w.ring.as<float>(),
                                               w.eps.as<float>(), w.noise.as<float>(), w.A.as<float>(),
                                               w.B.as<float>(), batch, d->D, w.partials.as<float>(),
                                               w.head_count.as<int32_t>(), head_slabs(d->D)};
@@ -1030,9 +1061,9 @@ extern "C" pd_status pd_sample_picard(const pd_schedule* s, const pd_denoiser* d
                         // the MLP's last layer also writes every row's Euler prediction
                         const HeunPredictArgs hp{dst, w.ring.as<float>(), w.A.as<float>(),
                                                  w.B.as<float>(), slots, w.xt.as<float>()};
-                        launch_linear_dense_predict(d->mlp_head(),
-                                                    d->mlp_trunk(src, w.scratch.as<float>(), st),
-                                                    src, hp, w.eps.as<float>(), st);
+                        launch_linear_out_predict(d->mlp_layer(3),
+                                                  d->mlp_trunk(src, w.scratch.as<float>(), st), src,
+                                                  hp, w.eps.as<float>(), st);
                     } else {
                         d->forward(src, w.eps.as<float>(), w.scratch.as<float>(), st);
                         if (s->heun)

@@ -105,6 +105,65 @@ def test_mlp_forward(shape, width, M):
     assert _rel(got, ref) <= REL_F32
 
 
+@pytest.mark.parametrize("D,width,scale", [
+    (160, 1024, 1.0),     # split layers, whole chunks
+    (36, 1100, 1.0),      # split, ragged chunks and feature tiles
+    (20, 512, 1e3),       # the shortest split layer; activations near 1e6
+    (24, 516, 1e-3),      # products far below the biases
+    (44, 508, 1.0),       # the longest fp32 layer, ragged
+    (4, 4, 1.0),          # one chunk, one feature tile, mostly padding
+])
+def test_mlp_tiles_match_float64(D, width, scale):
+    """Every tile shape (row counts around its edges), against float64: a float32 evaluation
+    rounds each product and sum, about sqrt(layers) 2^-24 sqrt(log2 K) of the result, 4e-7 here
+    (measured 2e-7 to 4.3e-7); 1e-6 is twice that.  A row's result does not depend on how many
+    rows are computed with it, and nothing is written past them."""
+    wl = _wl("mlp", (D,), width)
+    w = W.make_weights(wl.model)
+    w["W1"] = w["W1"] * np.float32(scale)
+    w["W2"] = w["W2"] * np.float32(scale)
+    sched, den = pd.from_workload(wl, w)
+    rng = np.random.default_rng(D)
+    x = rng.standard_normal((1040, D)).astype(np.float32)
+    n = rng.integers(0, 100, 1040).astype(np.int32)
+    tb = schedule.from_spec(wl.schedule)
+    ref = denoisers.Denoiser(wl.model, w, tb.alphabar, np.float64, False)(x.astype(np.float64), n)
+    whole = None
+    for M in (1040, 1024, 321, 257, 161, 129, 65, 64, 33, 17, 16, 15, 1):
+        out = torch.full((M + 1, D), 7.0, device="cuda")
+        pd.pd_denoiser_forward(den, _dev(x[:M]), _dev(n[:M]), out[:M])
+        got = out.cpu().numpy()
+        assert np.all(got[M] == 7.0), M
+        assert _rel(got[:M], ref[:M]) <= 1e-6, (M, _rel(got[:M], ref[:M]))
+        whole = got if whole is None else whole
+        assert np.array_equal(got[:M], whole[:M]), M
+
+
+@pytest.mark.parametrize("layer", ["W2", "W4"])
+def test_mlp_non_finite_weights_and_rows(layer):
+    """An infinite weight or input stays what a float32 evaluation makes of it, and leaves the
+    other rows and features alone."""
+    wl = _wl("mlp", (20,), 512)
+    w = W.make_weights(wl.model)
+    rng = np.random.default_rng(1)
+    x = rng.standard_normal((40, 20)).astype(np.float32)
+    n = np.zeros(40, np.int32)
+    clean = _forward(wl, w, x, n)
+    bad = dict(w, **{layer: w[layer].copy()})
+    bad[layer][3, 5] = np.inf
+    got = _forward(wl, bad, x, n)
+    if layer == "W4":                                # one feature only, infinite or NaN there
+        assert not np.isfinite(got[:, 3]).any()
+        keep = np.arange(20) != 3
+        assert np.isfinite(got[:, keep]).all() and _rel(got[:, keep], clean[:, keep]) <= 1e-6
+    else:
+        assert not np.isfinite(got).any()
+    x[7, 2] = np.inf
+    got = _forward(wl, w, x, n)
+    keep = np.arange(40) != 7
+    assert not np.isfinite(got[7]).any() and np.array_equal(got[keep], clean[keep])
+
+
 @pytest.mark.parametrize("shape,width,M,cond", [
     ((4, 8, 8), 32, 3, 0),        # two full pixel tiles per row
     ((4, 6, 7), 64, 5, 0),        # ragged last tile (42 pixels)
