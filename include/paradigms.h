@@ -256,7 +256,8 @@ typedef struct pd_sample_stats {
     int32_t time_kernels;      /* in: nonzero = bracket every denoiser, update and     */
                                /*     finalize launch with HIP events on `stream`      */
     int32_t denoiser_launches; /* out (with time_kernels): denoiser calls timed        */
-    int32_t update_launches;   /* out: Picard update (scan) or sequential step launches */
+    int32_t update_launches;   /* out: Picard update (scan) launches (sequential: 0, the
+                                  step is the denoiser's epilogue)                  */
     int32_t finalize_launches; /* out: stride/slide launches (Picard only)             */
     double denoiser_ms;        /* out: summed event time of the denoiser calls         */
     double update_ms;          /* out: summed event time of the update launches        */

@@ -16,9 +16,11 @@
 // feeds the MFMAs.  The two buffers are separate LDS variables: with one
 // array of two buffers the compiler cannot tell a read of one buffer from a
 // copy into the other, and waits for every copy to land before the next read.
+#include <cstddef>
 #include <cstring>
 #include <utility>
 
+#include "eps_out.h"
 #include "pd_internal.h"
 
 namespace pd {
@@ -61,6 +63,36 @@ struct ActVecs {
     static constexpr int F4 = ROWS * STRIDE / 4;
 };
 
+// The kernels' arguments, one struct so that a step's share of them can be read
+// where it is used: kept from the start they would hold some thirty scalar
+// registers through the whole kernel, which it does not have.
+struct ConvKernArgs {
+    ConvArgs a;
+    RowSrc src;
+    EpsOut eo;
+    int tiles_per_row;
+    int per;             // tiles per block and pass (tiles_per_pass) of all the rows
+};
+__device__ __forceinline__ EpsOut late_eps_out() {
+    typedef const __attribute__((address_space(4))) char* ConstPtr;
+    ConstPtr p = (ConstPtr)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *(const EpsOut*)(p + offsetof(ConvKernArgs, eo));
+}
+
+// Tiles that a block of `waves` waves takes a pass: the fewest that end in the
+// same number of passes over the launch's blocks.  The launch works it out for
+// all its rows; with fewer active ones (a shrunk window) the kernel does, by
+// counting up (a division would cost more than it saves).
+__host__ __device__ inline int tiles_per_pass(uint32_t ntiles, uint32_t blocks, int waves) {
+    uint32_t passes = 1;
+    while (passes < 8 && passes * blocks * waves < ntiles) ++passes;
+    if (passes * blocks * waves < ntiles) return waves;
+    int per = 1;
+    while (per * passes * blocks < ntiles) ++per;
+    return per;
+}
+
 // ---------------------------------------------------------------- bf16
 // k_conv_bf16: every matmul operand is bf16 (round to nearest even);
 // accumulation, bias, shift, SiLU and the guidance combination stay in fp32.
@@ -91,13 +123,16 @@ struct ConvLayoutBf16 {                          // units of 16 B (one lane's A 
     static constexpr __host__ __device__ int size(int i) { return i == 0 ? SL1 : SLM; }
 };
 
-template <int NB, int C>
+template <int NB, int C, bool STEP>
 __global__ __launch_bounds__(kBf16Waves * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void k_conv_bf16(ConvArgs a, RowSrc src, float* __restrict__ eps, int tiles_per_row) {
+void k_conv_bf16(ConvKernArgs ka) {
+    const ConvArgs& a = ka.a;
+    const RowSrc& src = ka.src;
+    const int tiles_per_row = ka.tiles_per_row;
     using L = ConvLayoutBf16<NB, C>;
     constexpr int NW = kBf16Waves;
     using AV = ActVecs<NB, NW>;
-    static_assert(C <= 8, "layer 1 holds at most 8 channels in one lane half");
+    static_assert(C == 4, "layer 1 holds the channels in one lane half, layer 4 in one register group");
     __shared__ bf8 lds_0[L::BUF];
     __shared__ bf8 lds_1[L::BUF];
     auto ldsb = [&](int buf) -> bf8* { return buf ? lds_1 : lds_0; };
@@ -259,7 +294,7 @@ void k_conv_bf16(ConvArgs a, RowSrc src, float* __restrict__ eps, int tiles_per_
                     if (br + 1 < nbranch) dma_shift(cur.n, br + 1);
                     else dma_shift(nxt.n, 0);
                 }
-                f16v o2[2] = {f16v{}, f16v{}};
+                    f16v o2[2] = {f16v{}, f16v{}};
                 static_for<NB>([&](auto bc) {
                     constexpr int b = decltype(bc)::value;
                     static_for<2>([&](auto gc) {
@@ -269,17 +304,23 @@ void k_conv_bf16(ConvArgs a, RowSrc src, float* __restrict__ eps, int tiles_per_
                     });
                 });
                 const f16v o = o2[0] + o2[1];
-                float* out = eps + cur.row * (int64_t)C * P;
+                const int64_t out = cur.row * (int64_t)C * P + cur.px;
+                EpsOut eo;
+                if constexpr (STEP) eo = late_eps_out();
+                auto put = [&](int c, float v) {
+                    if constexpr (STEP) eps_out(eo, out + c * P, v);
+                    else ka.eo.y[out + c * P] = v;
+                };
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const int c = 4 * half + r;
                     if (c < C) {
-                        const float v = o[r] + a.b4[c];
+                        const float v = o[r] + a.b4[r];
                         if (br == 0) {
                             eu[r] = v;
-                            if (nbranch == 1 && cur.active && cur.pxok) out[c * P + cur.px] = v;
+                            if (nbranch == 1 && cur.active && cur.pxok) put(c, v);
                         } else if (cur.active && cur.pxok) {
-                            out[c * P + cur.px] = eu[r] + a.guidance * (v - eu[r]);
+                            put(c, eu[r] + a.guidance * (v - eu[r]));
                         }
                     }
                 }
@@ -471,9 +512,18 @@ __device__ __forceinline__ uint32_t lds_addr(T* p) {
     return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) T*)p;
 }
 
-template <int NB, int C, bool GUIDED>
+//
+// Few tiles: the block's waves take `per` tiles a pass, as few as spread the
+// tiles over all the blocks in the same number of passes, and the waves
+// without one only copy weights.  A lone wave per SIMD runs its tile faster than
+// two that share the LDS: one 4x96x96 row (576 tiles) took 31.0 us on 72 compute
+// units with eight tiles each, and takes 22 us on 192 with three.
+template <int NB, int C, bool GUIDED, bool STEP>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void k_conv_f32s(ConvArgs a, RowSrc src, float* __restrict__ eps, int tiles_per_row) {
+void k_conv_f32s(ConvKernArgs ka) {
+    const ConvArgs& a = ka.a;
+    const RowSrc& src = ka.src;
+    const int tiles_per_row = ka.tiles_per_row;
     using L = LayoutS<NB, C>;
     constexpr int NW = 8;                          // waves per block, one tile each
     constexpr int NO = L::NO, KC = L::KC, W = 32 * NB;
@@ -491,9 +541,10 @@ void k_conv_f32s(ConvArgs a, RowSrc src, float* __restrict__ eps, int tiles_per_
     __shared__ __attribute__((aligned(16))) float vec[(NW + 2) * STRIDE];   // shifts, b2, b3
 
     const int groups = src.active ? *src.active : src.max_groups;
-    const int64_t ntiles = (int64_t)groups * src.group * tiles_per_row;
-    const int64_t ngroups = (ntiles + NW - 1) / NW;
-    if ((int64_t)blockIdx.x >= ngroups) return;              // uniform over the block
+    // fewer than 2^31 tiles: their rows would not fit the memory
+    const uint32_t ntiles = (uint32_t)groups * src.group * tiles_per_row;
+    const int per = groups == src.max_groups ? ka.per : tiles_per_pass(ntiles, gridDim.x, NW);
+    if (blockIdx.x * per >= ntiles) return;                  // uniform over the block
 
     const int tid = threadIdx.x, lane = tid & 63, lg = lane >> 4, lj = lane & 15;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -600,14 +651,15 @@ void k_conv_f32s(ConvArgs a, RowSrc src, float* __restrict__ eps, int tiles_per_
         const float* x;
         int n, px;
     };
-    auto locate = [&](int64_t tg) -> Tile {
+    auto locate = [&](uint32_t tg) -> Tile {
         Tile T;
-        const int64_t t = tg * NW + wave;
+        const uint32_t t = tg * per + wave;
         T.active = t < ntiles;
-        const int64_t tt = T.active ? t : ntiles - 1;       // idle waves redo the last tile
-        T.row = tt / tiles_per_row;
-        const int pt = (int)(tt % tiles_per_row);
-        const int g = (int)(T.row / src.group), bb = (int)(T.row % src.group);
+        const uint32_t tt = T.active ? t : ntiles - 1;      // a wave past the end redoes the last tile
+        const uint32_t row = tt / (uint32_t)tiles_per_row;
+        T.row = row;
+        const int pt = (int)(tt - row * tiles_per_row);
+        const int g = (int)(row / (uint32_t)src.group), bb = (int)(row - g * src.group);
         const int64_t sl = src.slot ? __builtin_amdgcn_readfirstlane(src.slot[g]) : g;
         T.x = src.base + sl * src.slot_stride + (int64_t)bb * C * P;
         T.n = __builtin_amdgcn_readfirstlane(row_timestep(src, g));
@@ -628,13 +680,31 @@ void k_conv_f32s(ConvArgs a, RowSrc src, float* __restrict__ eps, int tiles_per_
         vec[(NW + 1) * STRIDE + i] = a.b3[i];
     }
     land();
+    if (wave >= per) {
+        // no tile for this wave: its share of the copies, and the same barriers
+        // and waits as the passes below (the same number of its own copies is in
+        // flight at each)
+        int rot = 0;
+        for (uint32_t tg = blockIdx.x; tg * per < ntiles; tg += gridDim.x)
+            for (int br = 0; br < nbranch; ++br) {
+                const bool more = br + 1 < nbranch || (tg + gridDim.x) * per < ntiles;
+#pragma unroll 1
+                for (int s = 0; s < NS; ++s) {
+                    if (s == 0 || (s + 1 == NS && !more)) land();
+                    else land_but_next();
+                    if (s + 2 < NS || more) dma_slab(s + 2 < NS ? s + 2 : s + 2 - NS, (rot + s + 2) % 3);
+                }
+                rot = (rot + NS) % 3;
+            }
+        return;
+    }
     float xin = load_x(cur);
     // slab s of the current pass sits in buffer (rot + s) % 3
     int rot = 0;
 
-    for (int64_t tg = blockIdx.x; tg < ngroups; tg += gridDim.x) {
-        const bool last_group = tg + gridDim.x >= ngroups;
-        const int64_t tg_next = last_group ? tg : tg + gridDim.x;
+    for (uint32_t tg = blockIdx.x; tg * per < ntiles; tg += gridDim.x) {
+        const bool last_group = (tg + gridDim.x) * per >= ntiles;
+        const uint32_t tg_next = last_group ? tg : tg + gridDim.x;
         f4 eu = f4{0.f, 0.f, 0.f, 0.f};
         float xnx = 0.f;
         for (int br = 0; br < nbranch; ++br) {
@@ -757,17 +827,23 @@ void k_conv_f32s(ConvArgs a, RowSrc src, float* __restrict__ eps, int tiles_per_
             }
             // lanes 0..15 hold channel r of pixel l in register r
             if (lane < 16) {
-                float* out = eps + cur.row * (int64_t)C * P;
+                const int64_t out = cur.row * (int64_t)C * P + cur.px;
+                EpsOut eo;
+                if constexpr (STEP) eo = late_eps_out();
+                auto put = [&](int r, float v) {
+                    if constexpr (STEP) eps_out(eo, out + r * P, v);
+                    else ka.eo.y[out + r * P] = v;
+                };
 #pragma unroll
                 for (int r = 0; r < C; ++r) {
                     const float v = __builtin_fmaf(o4[r], invS, a.b4[r]);
                     const bool store = cur.active && cur.px < P;
                     if constexpr (!GUIDED) {
-                        if (store) out[(int64_t)r * P + cur.px] = v;
+                        if (store) put(r, v);
                     } else if (br == 0) {
                         eu[r] = v;
                     } else if (store) {
-                        out[(int64_t)r * P + cur.px] = eu[r] + a.guidance * (v - eu[r]);
+                        put(r, eu[r] + a.guidance * (v - eu[r]));
                     }
                 }
             }
@@ -861,30 +937,39 @@ void pack_s_t(const float* W1, const float* W2, const float* W3, const float* W4
 }
 
 template <int NB, int C>
-void launch_s_t(const ConvArgs& a, const RowSrc& src, float* eps, hipStream_t s) {
+void launch_s_t(const ConvArgs& a, const RowSrc& src, const EpsOut& out, hipStream_t s) {
     const int tiles_per_row = (int)((a.P + 15) / 16);
     const int64_t ntiles = (int64_t)src.max_groups * src.group * tiles_per_row;
     if (ntiles == 0) return;
-    int64_t blocks = (ntiles + 7) / 8;                       // persistent: one block per CU
-    if (blocks > device_cus()) blocks = device_cus();
-    if (a.shift_c)
-        hipLaunchKernelGGL((k_conv_f32s<NB, C, true>), dim3((unsigned)blocks), dim3(512), 0, s, a, src, eps,
-                           tiles_per_row);
+    if (ntiles >= (int64_t)1 << 31) fail(PD_ERR_UNSUPPORTED, "conv1x1: too many pixel tiles");
+    const int64_t blocks = ntiles < device_cus() ? ntiles : device_cus();   // persistent: one block per CU
+    const dim3 grid((unsigned)blocks), block(512);
+    const ConvKernArgs ka{a, src, out, tiles_per_row, tiles_per_pass((uint32_t)ntiles, (uint32_t)blocks, 8)};
+    const bool step = out.mode != EPS_STORE;
+    if (a.shift_c && step)
+        hipLaunchKernelGGL((k_conv_f32s<NB, C, true, true>), grid, block, 0, s, ka);
+    else if (a.shift_c)
+        hipLaunchKernelGGL((k_conv_f32s<NB, C, true, false>), grid, block, 0, s, ka);
+    else if (step)
+        hipLaunchKernelGGL((k_conv_f32s<NB, C, false, true>), grid, block, 0, s, ka);
     else
-        hipLaunchKernelGGL((k_conv_f32s<NB, C, false>), dim3((unsigned)blocks), dim3(512), 0, s, a, src, eps,
-                           tiles_per_row);
+        hipLaunchKernelGGL((k_conv_f32s<NB, C, false, false>), grid, block, 0, s, ka);
     PD_HIP(hipGetLastError());
 }
 
 template <int NB, int C>
-void launch_bf16_t(const ConvArgs& a, const RowSrc& src, float* eps, hipStream_t s) {
+void launch_bf16_t(const ConvArgs& a, const RowSrc& src, const EpsOut& out, hipStream_t s) {
     const int tiles_per_row = (int)((a.P + 31) / 32);
     const int64_t ntiles = (int64_t)src.max_groups * src.group * tiles_per_row;
     if (ntiles == 0) return;
     int64_t blocks = (ntiles + kBf16Waves - 1) / kBf16Waves;   // persistent: two blocks per CU
     if (blocks > 2 * device_cus()) blocks = 2 * device_cus();
-    hipLaunchKernelGGL((k_conv_bf16<NB, C>), dim3((unsigned)blocks), dim3(kBf16Waves * 64), 0, s, a,
-                       src, eps, tiles_per_row);
+    const dim3 grid((unsigned)blocks), block(kBf16Waves * 64);
+    const ConvKernArgs ka{a, src, out, tiles_per_row, kBf16Waves};
+    if (out.mode != EPS_STORE)
+        hipLaunchKernelGGL((k_conv_bf16<NB, C, true>), grid, block, 0, s, ka);
+    else
+        hipLaunchKernelGGL((k_conv_bf16<NB, C, false>), grid, block, 0, s, ka);
     PD_HIP(hipGetLastError());
 }
 
@@ -924,13 +1009,13 @@ void conv_pack_weights(int C, int width, bool bf16, const float* W1, const float
     fail(PD_ERR_UNSUPPORTED, "conv1x1: unsupported channel count / width");
 }
 
-void launch_conv1x1(const ConvArgs& a, const RowSrc& src, float* eps, hipStream_t s) {
+void launch_conv1x1(const ConvArgs& a, const RowSrc& src, const EpsOut& out, hipStream_t s) {
 #define X(nb, c)                                                   \
     if (a.C == c && a.width == 32 * nb) {                          \
         if (a.bf16)                                                \
-            launch_bf16_t<nb, c>(a, src, eps, s);                  \
+            launch_bf16_t<nb, c>(a, src, out, s);                  \
         else                                                       \
-            launch_s_t<nb, c>(a, src, eps, s);                     \
+            launch_s_t<nb, c>(a, src, out, s);                     \
         return;                                                    \
     }
     PD_CONV_SHAPES(X)

@@ -4,6 +4,7 @@
 // per-timestep constants are float tables built in double on the host.
 // For this model the whole sampling loop (Picard or sequential) also runs in
 // a single workgroup: the state is a few KB and fits in LDS.
+#include "eps_out.h"
 #include "gmm.h"
 #include "pd_internal.h"
 #include "philox.h"
@@ -117,8 +118,7 @@ __device__ __forceinline__ void gmm_eps_row(const GmmParams& g, int n, float x0,
     gmm_eps_core(MeansMem{g.means}, g.K, g.a[n], g.inv2s2[n], g.coef[n], x0, x1, e0, e1);
 }
 
-__global__ __launch_bounds__(256) void k_gmm_eps(GmmParams g, RowSrc src,
-                                                 float* __restrict__ eps) {
+__global__ __launch_bounds__(256) void k_gmm_eps(GmmParams g, RowSrc src, EpsOut out) {
     const int groups = src.active ? *src.active : src.max_groups;
     const int64_t rows = (int64_t)groups * src.group;
     const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -128,12 +128,8 @@ __global__ __launch_bounds__(256) void k_gmm_eps(GmmParams g, RowSrc src,
     const float* x = src.base + sl * src.slot_stride + (int64_t)b * 2;
     float e0, e1;
     gmm_eps_row(g, row_timestep(src, gi), x[0], x[1], e0, e1);
-    eps[r * 2] = e0;
-    eps[r * 2 + 1] = e1;
-}
-
-__device__ __forceinline__ float drift(float A, float x, float B, float e) {
-    return __fadd_rn(__fmul_rn(A, x), __fmul_rn(B, e));
+    eps_out(out, r * 2, e0);
+    eps_out(out, r * 2 + 1, e1);
 }
 
 // Inclusive prefix sum over the 64 lanes of a wave (every lane active): four
@@ -488,12 +484,12 @@ void launch_gmm_sequential_loop(const GmmLoopArgs& a, hipStream_t s) {
     PD_HIP(hipGetLastError());
 }
 
-void launch_gmm_eps(const GmmParams& g, const RowSrc& src, float* eps, hipStream_t s) {
+void launch_gmm_eps(const GmmParams& g, const RowSrc& src, const EpsOut& out, hipStream_t s) {
     if (g.K > kMaxK) fail(PD_ERR_UNSUPPORTED, "gmm2d supports at most 64 components");
     const int64_t rows = (int64_t)src.max_groups * src.group;
     if (rows == 0) return;
     hipLaunchKernelGGL(k_gmm_eps, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, s, g, src,
-                       eps);
+                       out);
     PD_HIP(hipGetLastError());
 }
 

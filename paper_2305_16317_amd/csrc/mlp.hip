@@ -2,6 +2,7 @@
 // per output tile (the tile itself is computed in linear_tile.h).  A layer is
 // bound by the loads of its busiest compute unit and by the latency around
 // them, so the launch picks the tile by the rows and features it has.
+#include "eps_out.h"
 #include "linear_tile.h"
 #include "mlp.h"
 
@@ -44,12 +45,11 @@ __global__ __launch_bounds__(kLinThreads) void k_linear(LinearArgs a, RowSrc src
     }
 }
 
-// The last layer: epsilon, row-major.  With h, each output's Euler prediction
-// follows (Heun's first stage): the drift A_m x + B_m eps with two rounded
-// products and a rounded sum, as the scan's drift does.
+// The last layer: epsilon, row-major, or the step that follows it.  With h,
+// each output's Euler prediction in the window (Heun's first stage).
 template <int RT, int CT, bool SPLIT, bool PREDICT>
 __global__ __launch_bounds__(kLinThreads) void k_linear_out(LinearArgs a, RowSrc src, HiddenBuf in,
-                                                            HeunPredictArgs h, float* __restrict__ y) {
+                                                            HeunPredictArgs h, EpsOut out) {
     __shared__ LinearLds<RT, CT> lds;
     const int mt0 = blockIdx.y * RT, nt0 = blockIdx.x * CT;
     const int M = (src.active ? *src.active : src.max_groups) * src.group, N = a.N;
@@ -58,16 +58,17 @@ __global__ __launch_bounds__(kLinThreads) void k_linear_out(LinearArgs a, RowSrc
             const int row = 16 * (mt0 + tile / CT) + ((threadIdx.x >> 2) & 15);
             const int n = 16 * (nt0 + tile % CT) + 4 * ((threadIdx.x >> 6) & 3) + (threadIdx.x & 3);
             if (row >= M || n >= N) return;
-            y[(int64_t)row * N + n] = e;
-            if constexpr (PREDICT) {
+            if constexpr (!PREDICT) {
+                eps_out(out, (int64_t)row * N + n, e);
+            } else {
+                out.y[(int64_t)row * N + n] = e;
                 const LoopState cur = *h.st;
                 const int j = row / src.group, b = row % src.group;
                 const int m = cur.t + j;
                 const int64_t BD = (int64_t)src.group * N;
                 const int64_t c = (int64_t)b * N + n;
                 const float x = h.ring[(int64_t)((m <= cur.f ? m : cur.f) % h.ring_slots) * BD + c];
-                const float dr = __fadd_rn(__fmul_rn(h.A[m], x), __fmul_rn(h.B[m], e));
-                h.xt[(int64_t)j * BD + c] = __fadd_rn(x, dr);
+                h.xt[(int64_t)j * BD + c] = __fadd_rn(x, drift(h.A[m], x, h.B[m], e));
             }
         });
 }
@@ -188,16 +189,16 @@ void launch_hidden(const LinearArgs& a, const RowSrc& rows, const HiddenBuf& in,
 }
 
 template <bool PREDICT>
-void launch_out(const LinearArgs& a, const HiddenBuf& in, const RowSrc& rows, const HeunPredictArgs& h, float* y,
-                hipStream_t s) {
+void launch_out(const LinearArgs& a, const HiddenBuf& in, const RowSrc& rows, const HeunPredictArgs& h,
+                const EpsOut& out, hipStream_t s) {
     const int64_t M = (int64_t)rows.max_groups * rows.group;
     if (M == 0) return;
     check_sizes(a);
     with_tile(M, a.N, [&](auto rt, auto ct, dim3 grid) {
         constexpr int RT = decltype(rt)::value, CT = decltype(ct)::value;
         const dim3 block(kLinThreads);
-        if (a.wscale) hipLaunchKernelGGL((k_linear_out<RT, CT, true, PREDICT>), grid, block, 0, s, a, rows, in, h, y);
-        else hipLaunchKernelGGL((k_linear_out<RT, CT, false, PREDICT>), grid, block, 0, s, a, rows, in, h, y);
+        if (a.wscale) hipLaunchKernelGGL((k_linear_out<RT, CT, true, PREDICT>), grid, block, 0, s, a, rows, in, h, out);
+        else hipLaunchKernelGGL((k_linear_out<RT, CT, false, PREDICT>), grid, block, 0, s, a, rows, in, h, out);
     });
     PD_HIP(hipGetLastError());
 }
@@ -230,13 +231,14 @@ void launch_linear_hidden(const LinearArgs& a, const HiddenBuf& in, const RowSrc
     launch_hidden<false>(a, rows, in, 0, out, s);
 }
 
-void launch_linear_out(const LinearArgs& a, const HiddenBuf& in, const RowSrc& rows, float* y, hipStream_t s) {
-    launch_out<false>(a, in, rows, HeunPredictArgs{}, y, s);
+void launch_linear_out(const LinearArgs& a, const HiddenBuf& in, const RowSrc& rows, const EpsOut& out,
+                       hipStream_t s) {
+    launch_out<false>(a, in, rows, HeunPredictArgs{}, out, s);
 }
 
 void launch_linear_out_predict(const LinearArgs& a, const HiddenBuf& in, const RowSrc& rows, const HeunPredictArgs& h,
                                float* y, hipStream_t s) {
-    launch_out<true>(a, in, rows, h, y, s);
+    launch_out<true>(a, in, rows, h, eps_store(y), s);
 }
 
 }  // namespace pd

@@ -107,6 +107,34 @@ __device__ inline void picard_init_body(const PicardInit& a) {
     }
 }
 
+// What a denoiser launch does with its epsilon (row-major over its rows).  The
+// sequential samplers' steps run where epsilon is formed: x and the other
+// arrays are indexed as epsilon is.
+enum EpsMode {
+    EPS_STORE = 0,       // y = eps
+    EPS_STEP = 1,        // x <- x + (A x + B eps) [+ z]
+    EPS_PREDICT = 2,     // y = eps, xt = x + (A x + B eps)
+    EPS_STEP_HEUN = 3,   // EPS_STEP with (eps1 + eps) / 2
+    EPS_STEP_DPM = 4,    // x <- x + (((A x + B eps) + R xp) + S ep) (R = 0: the
+                         // first-order step), then (xp, ep) <- (x, eps)
+};
+struct EpsOut {
+    int32_t mode;
+    float* y;
+    float* x;
+    const float* z;      // or nullptr
+    const float* eps1;
+    float* xt;
+    float* xp;
+    float* ep;
+    float A, B, R, S;
+};
+inline EpsOut eps_store(float* y) {
+    EpsOut o{};
+    o.y = y;
+    return o;
+}
+
 // ---------------------------------------------------------------- kernels
 // rng.hip
 void launch_normals(uint64_t seed, uint32_t rng_stream, int64_t count, const float* scale,
@@ -128,7 +156,7 @@ struct GmmParams {
     const float* coef;    // [T_train] sqrt(1 - abar_n) / s_n^2
     int32_t K;
 };
-void launch_gmm_eps(const GmmParams& g, const RowSrc& src, float* eps, hipStream_t s);
+void launch_gmm_eps(const GmmParams& g, const RowSrc& src, const EpsOut& out, hipStream_t s);
 // The whole Picard (or sequential) loop of the mixture model in one workgroup.
 struct GmmLoopArgs {
     GmmParams g;
@@ -180,7 +208,8 @@ void launch_pack_linear(const float* W, int N, int K, float* out, float* wscale,
 void launch_linear_first(const LinearArgs& a, const RowSrc& src, int64_t D, const HiddenBuf& out, hipStream_t s);
 void launch_linear_hidden(const LinearArgs& a, const HiddenBuf& in, const RowSrc& rows, const HiddenBuf& out,
                           hipStream_t s);
-void launch_linear_out(const LinearArgs& a, const HiddenBuf& in, const RowSrc& rows, float* y, hipStream_t s);
+void launch_linear_out(const LinearArgs& a, const HiddenBuf& in, const RowSrc& rows, const EpsOut& out,
+                       hipStream_t s);
 
 // conv.hip: per-pixel 4-layer stack with fp32 or bf16 MFMA.
 // The kernels take the argument of e^-u in base 2, t = kNegLog2e u, as their
@@ -193,7 +222,8 @@ struct ConvArgs {
     const float* shift_c;   // [T_train][W] kNegLog2e (b1 + e_n + Wc c), or nullptr
     const float* b2;        // [W] kNegLog2e b2
     const float* b3;        // [W] kNegLog2e b3
-    const float* b4;
+    float b4[4];            // by value: a load at the end of a pass would wait for
+                            // the weight copies in flight
     float guidance;
     int32_t C;              // channels
     int32_t width;          // hidden width W
@@ -204,18 +234,13 @@ size_t conv_frag_bytes(int C, int width, bool bf16);
 void conv_pack_weights(int C, int width, bool bf16, const float* W1, const float* W2,
                        const float* W3, const float* W4, std::vector<uint8_t>& out);
 bool conv_supported(int C, int width, bool bf16);
-void launch_conv1x1(const ConvArgs& a, const RowSrc& src, float* eps, hipStream_t s);
+void launch_conv1x1(const ConvArgs& a, const RowSrc& src, const EpsOut& out, hipStream_t s);
 
 // picard.hip
 // Heun on the window: Euler prediction of every row (the scan averages the
 // two evaluations, launch_picard_scan's eps2).
 void launch_heun_predict(const LoopState* st, const float* ring, const float* eps, const float* A,
                          const float* B, int p, int64_t BD, float* xt, hipStream_t s);
-void launch_seq_heun_predict(const float* x, const float* eps, float A, float B, int64_t n,
-                             float* xt, hipStream_t s);
-void launch_seq_heun_combine(float* eps, const float* eps2, int64_t n, hipStream_t s);
-void launch_seq_step_dpm(float* x, const float* eps, float* xp, float* ep, float P, float Q, float R,
-                         float S, bool second, int64_t n, hipStream_t s);
 // Blocks per sample of the scan (one column range each; the partial sums
 // come per block) and the columns each covers.
 int picard_partial_blocks(int64_t D, int batch);
@@ -277,7 +302,4 @@ struct HeadScanArgs {
 };
 bool mlp_head_scan_fits(int p);
 void launch_mlp_head_scan(const HeadScanArgs& a, const FinalizeArgs& fin, hipStream_t s);
-void launch_seq_step(float* x, const float* eps, const float* z, float A, float B, int64_t n,
-                     hipStream_t s);
-
 }  // namespace pd

@@ -12,6 +12,7 @@
 // copies the state into mapped host memory for the host's batch decisions.
 #include <type_traits>
 
+#include "eps_out.h"
 #include "linear_tile.h"
 #include "pd_internal.h"
 
@@ -68,11 +69,6 @@ __device__ __forceinline__ float group_sum(float v) {
     if constexpr (N >= 32) v += __shfl_xor(v, 16, 64);
     if constexpr (N >= 64) v += __shfl_xor(v, 32, 64);
     return v;
-}
-
-__device__ __forceinline__ float drift(float A, float x, float B, float e) {
-    // y = A x + B eps, two products and one sum, each rounded (no contraction)
-    return __fadd_rn(__fmul_rn(A, x), __fmul_rn(B, e));
 }
 
 // Heun's method, window side (rows j < p_eff of the current window):
@@ -597,53 +593,6 @@ __global__ __launch_bounds__(NW * 64) void k_picard_scan(
 }
 
 
-// Heun's method, sequential side: the Euler prediction of one step, and the
-// averaged epsilon (both as in the window kernels above).
-__global__ __launch_bounds__(256) void k_seq_heun_predict(const float* __restrict__ x,
-                                                          const float* __restrict__ eps, float A,
-                                                          float B, int64_t n,
-                                                          float* __restrict__ xt) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    xt[i] = __fadd_rn(x[i], drift(A, x[i], B, eps[i]));
-}
-
-__global__ __launch_bounds__(256) void k_seq_heun_combine(float* __restrict__ eps,
-                                                          const float* __restrict__ eps2,
-                                                          int64_t n) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    eps[i] = __fmul_rn(__fadd_rn(eps[i], eps2[i]), 0.5f);
-}
-
-// DPM-Solver, sequential side: x <- x + (((P x + Q eps) + R xp) + S ep) on a
-// second-order step (else the first-order drift), then (xp, ep) <- (x, eps).
-__global__ __launch_bounds__(256) void k_seq_step_dpm(float* __restrict__ x,
-                                                      const float* __restrict__ eps,
-                                                      float* __restrict__ xp,
-                                                      float* __restrict__ ep, float P, float Q,
-                                                      float R, float S, int second, int64_t n) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const float xi = x[i], ei = eps[i];
-    float y = drift(P, xi, Q, ei);
-    if (second) y = __fadd_rn(__fadd_rn(y, __fmul_rn(R, xp[i])), __fmul_rn(S, ep[i]));
-    x[i] = __fadd_rn(xi, y);
-    xp[i] = xi;
-    ep[i] = ei;
-}
-
-__global__ __launch_bounds__(256) void k_seq_step(float* __restrict__ x,
-                                                  const float* __restrict__ eps,
-                                                  const float* __restrict__ z, float A, float B,
-                                                  int64_t n) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    float v = __fadd_rn(x[i], drift(A, x[i], B, eps[i]));
-    if (z) v = __fadd_rn(v, z[i]);
-    x[i] = v;
-}
-
 }  // namespace
 
 // A block covers at most 64 lanes x VEC columns.  When the grid takes more
@@ -677,29 +626,6 @@ void launch_heun_predict(const LoopState* st, const float* ring, const float* ep
                          const float* B, int p, int64_t BD, float* xt, hipStream_t s) {
     hipLaunchKernelGGL(k_heun_predict, dim3(stream_blocks((int64_t)p * BD)), dim3(256), 0, s, st,
                        ring, eps, A, B, p, BD, xt);
-    PD_HIP(hipGetLastError());
-}
-
-void launch_seq_heun_predict(const float* x, const float* eps, float A, float B, int64_t n,
-                             float* xt, hipStream_t s) {
-    if (n <= 0) return;
-    hipLaunchKernelGGL(k_seq_heun_predict, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, x,
-                       eps, A, B, n, xt);
-    PD_HIP(hipGetLastError());
-}
-
-void launch_seq_step_dpm(float* x, const float* eps, float* xp, float* ep, float P, float Q, float R,
-                         float S, bool second, int64_t n, hipStream_t s) {
-    if (n <= 0) return;
-    hipLaunchKernelGGL(k_seq_step_dpm, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, x, eps, xp,
-                       ep, P, Q, R, S, (int)second, n);
-    PD_HIP(hipGetLastError());
-}
-
-void launch_seq_heun_combine(float* eps, const float* eps2, int64_t n, hipStream_t s) {
-    if (n <= 0) return;
-    hipLaunchKernelGGL(k_seq_heun_combine, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, eps,
-                       eps2, n);
     PD_HIP(hipGetLastError());
 }
 
@@ -766,15 +692,6 @@ void launch_mlp_head_scan(const HeadScanArgs& a, const FinalizeArgs& fin, hipStr
 void launch_picard_finalize(const FinalizeArgs& fin, hipStream_t s) {
     hipLaunchKernelGGL(k_picard_finalize, dim3(1), dim3(1024), 0, s, fin,
                        picard_partial_blocks(fin.D, fin.batch));
-    PD_HIP(hipGetLastError());
-}
-
-
-void launch_seq_step(float* x, const float* eps, const float* z, float A, float B, int64_t n,
-                     hipStream_t s) {
-    if (n <= 0) return;
-    hipLaunchKernelGGL(k_seq_step, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, x, eps, z,
-                       A, B, n);
     PD_HIP(hipGetLastError());
 }
 

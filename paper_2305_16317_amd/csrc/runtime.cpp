@@ -345,6 +345,7 @@ struct pd_denoiser {
     DevBuf W[4], bias[4], shift1, wscale[4];
     // conv1x1
     DevBuf frags, shift_u, shift_c;
+    float b4[4] = {0.f, 0.f, 0.f, 0.f};
     // pd_denoiser_forward's MLP scratch (kForwardRows rows).  Calls may come
     // from several threads and streams: under fwd_mu, each call's kernels wait
     // for fwd_done, the end of the previous call's use, and record it anew.
@@ -386,21 +387,24 @@ struct pd_denoiser {
     }
 
     void forward(const RowSrc& src, float* eps, float* scratch, hipStream_t s) const {
+        forward(src, eps_store(eps), scratch, s);
+    }
+    void forward(const RowSrc& src, const EpsOut& out, float* scratch, hipStream_t s) const {
         switch (desc.kind) {
             case PD_MODEL_GMM2D:
-                launch_gmm_eps(gmm(), src, eps, s);
+                launch_gmm_eps(gmm(), src, out, s);
                 break;
             case PD_MODEL_MLP:
-                launch_linear_out(mlp_layer(3), mlp_trunk(src, scratch, s), src, eps, s);
+                launch_linear_out(mlp_layer(3), mlp_trunk(src, scratch, s), src, out, s);
                 break;
             case PD_MODEL_CONV1X1: {
                 ConvArgs a{frags.p,           shift_u.as<float>(),
                            guided() ? shift_c.as<float>() : nullptr,
-                           bias[1].as<float>(), bias[2].as<float>(), bias[3].as<float>(),
+                           bias[1].as<float>(), bias[2].as<float>(), {b4[0], b4[1], b4[2], b4[3]},
                            desc.guidance,     C,
                            desc.width,        P,
                            desc.dtype == PD_BF16 ? 1 : 0};
-                launch_conv1x1(a, src, eps, s);
+                launch_conv1x1(a, src, out, s);
                 break;
             }
             default:
@@ -509,14 +513,15 @@ static void create_denoiser(const pd_model_desc& m, const int64_t* shape, int32_
     const float* W4 = w[6];
     d.bias[1].upload(w[3], Wd);
     d.bias[2].upload(w[5], Wd);
-    d.bias[3].upload(w[7], (size_t)Din);
     if (m.kind == PD_MODEL_MLP) {
+        d.bias[3].upload(w[7], (size_t)Din);
         pack_mlp(d, W1, W2, W3, W4);
         d.shift1.upload(sh.data(), sh.size());
         d.fwd_scratch.alloc(d.scratch_floats(kForwardRows) * sizeof(float));
         PD_HIP(hipEventCreateWithFlags(&d.fwd_done, hipEventDisableTiming));
         return;
     }
+    for (int c = 0; c < d.C && c < 4; ++c) d.b4[c] = w[7][c];
     std::vector<uint8_t> packed;
     conv_pack_weights(d.C, Wd, m.dtype == PD_BF16, W1, W2, W3, W4, packed);
     d.frags.upload(packed.data(), packed.size());
@@ -916,26 +921,35 @@ extern "C" pd_status pd_sample_sequential(const pd_schedule* s, const pd_denoise
         tm.mark(-1);
         int64_t evals = 0;
         for (int i = 0; i < s->T; ++i) {
-            const RowSrc src{x, nullptr, BD, batch, 1, w.model_t.as<int32_t>() + i, nullptr, d->T_train - 1};
-            d->forward(src, w.eps.as<float>(), w.scratch.as<float>(), st);
-            ++evals;
-            if (s->heun && i + 1 < s->T) {     // Heun: second evaluation at the Euler prediction
-                launch_seq_heun_predict(x, w.eps.as<float>(), s->A[i], s->B[i], BD, w.xt.as<float>(), st);
-                const RowSrc src2{w.xt.as<float>(), nullptr, BD, batch, 1,
-                                  w.model_t_next.as<int32_t>() + i, nullptr, d->T_train - 1};
-                d->forward(src2, w.eps2.as<float>(), w.scratch.as<float>(), st);
-                launch_seq_heun_combine(w.eps.as<float>(), w.eps2.as<float>(), BD, st);
-                ++evals;
-            }
-            tm.mark(CAT_DENOISER);
+            RowSrc src{x, nullptr, BD, batch, 1, w.model_t.as<int32_t>() + i, nullptr, d->T_train - 1};
+            // the step is the denoiser's epilogue
+            EpsOut out{};
+            out.y = w.eps.as<float>();
+            out.x = x;
+            out.A = s->A[i];
+            out.B = s->B[i];
             if (s->dpm) {
-                launch_seq_step_dpm(x, w.eps.as<float>(), w.xprev.as<float>(), w.eprev.as<float>(),
-                                    s->A[i], s->B[i], s->R[i], s->S[i], s->R[i] != 0.f, BD, st);
+                out.mode = EPS_STEP_DPM;
+                out.xp = w.xprev.as<float>();
+                out.ep = w.eprev.as<float>();
+                out.R = s->R[i];
+                out.S = s->S[i];
+            } else if (s->heun && i + 1 < s->T) {   // Heun: second evaluation at the Euler prediction
+                out.mode = EPS_PREDICT;
+                out.xt = w.xt.as<float>();
+                d->forward(src, out, w.scratch.as<float>(), st);
+                ++evals;
+                src.base = w.xt.as<float>();
+                src.n = w.model_t_next.as<int32_t>() + i;
+                out.mode = EPS_STEP_HEUN;
+                out.eps1 = w.eps.as<float>();
             } else {
-                const float* z = w.noise.p ? w.noise.as<float>() + (int64_t)i * BD : nullptr;
-                launch_seq_step(x, w.eps.as<float>(), z, s->A[i], s->B[i], BD, st);
+                out.mode = EPS_STEP;
+                out.z = w.noise.p ? w.noise.as<float>() + (int64_t)i * BD : nullptr;
             }
-            tm.mark(CAT_UPDATE);
+            d->forward(src, out, w.scratch.as<float>(), st);
+            ++evals;
+            tm.mark(CAT_DENOISER);
         }
         PD_HIP(hipMemcpyAsync(x_out, x, sizeof(float) * BD, hipMemcpyDeviceToDevice, st));
         PD_HIP(hipStreamSynchronize(st));

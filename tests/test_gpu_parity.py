@@ -185,6 +185,21 @@ def test_conv1x1_forward(shape, width, M, cond):
     assert _rel(got, ref) <= REL_F32
 
 
+@pytest.mark.parametrize("dtype,cond", [("f32", 0), ("f32", 24), ("bf16", 24)])
+def test_conv1x1_rows_do_not_depend_on_the_batch(dtype, cond):
+    """From one tile a block to several passes (96 x 96 pixels are 576 or 288 tiles a row), the
+    tiles are shared out differently and computed alike."""
+    wl = _wl("conv1x1", (4, 96, 96), 64, T=1000, cond=cond, dtype=dtype)
+    w = W.make_weights(wl.model)
+    rng = np.random.default_rng(4)
+    x = rng.standard_normal((18, wl.model.D)).astype(np.float32)
+    n = rng.integers(0, 1000, 18).astype(np.int32)
+    whole = _forward(wl, w, x, n)
+    assert np.isfinite(whole).all()
+    for M in (1, 2, 3, 4, 5, 8, 9, 13):
+        assert np.array_equal(_forward(wl, w, x[:M], n[:M]), whole[:M]), M
+
+
 @pytest.mark.parametrize("w1_scale,w2_scale", [(1, 1e-6), (1, 1e-3), (1, 1e2), (100, 1e3)])
 def test_conv1x1_fp32_hidden_scales(w1_scale, w2_scale):
     """Hidden activations far below fp16's range (W2 scaled down: layer-3
