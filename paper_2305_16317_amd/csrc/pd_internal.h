@@ -62,6 +62,8 @@ struct LoopState {
 };
 // The host reads the loop state from a copy in mapped, coherent pinned host
 // memory that the kernels write as they change it (no copy launch per batch).
+// It reads it after an event or stream synchronisation, whose release makes the
+// stores visible: a system-scope fence here cost each iteration over 1 us.
 __device__ inline void mirror_state(const LoopState& v, LoopState* host) {
     if (!host) return;
     host->t = v.t;
@@ -72,7 +74,6 @@ __device__ inline void mirror_state(const LoopState& v, LoopState* host) {
     host->first_stride = v.first_stride;
     host->nrows = v.nrows;
     host->evals = v.evals;
-    __threadfence_system();
 }
 
 // The start of a Picard run: the loop state and the first window's row
@@ -280,26 +281,4 @@ bool launch_picard_scan(const LoopState* st, float* ring, const float* eps, cons
                         int batch, int64_t D, float* partials, const FinalizeArgs& fin,
                         const float* eps2, hipStream_t s);
 void launch_picard_finalize(const FinalizeArgs& fin, hipStream_t s);
-// The MLP's last layer fused with the Picard update, error and finalize (Euler
-// drift, no history row): one launch in place of the last layer, the scan and
-// the finalize step.  partials holds [batch][p][n_slabs]; count holds
-// n_slabs + 1 ints, zero between launches.
-struct HeadScanArgs {
-    LinearArgs l4;          // the last layer: W4 [D][W], b4, no activation
-    HiddenBuf h;            // the third layer's output
-    RowSrc rows;            // the window's rows (the layer's row count)
-    const LoopState* st;
-    float* ring;
-    float* eps;             // [rows][D] epsilon, written and read back
-    const float* noise;     // [T][batch][D] or nullptr
-    const float* A;
-    const float* B;
-    int32_t batch;
-    int64_t D;
-    float* partials;
-    int32_t* count;
-    int32_t n_slabs;        // 16-column slabs, ceil(D / 16)
-};
-bool mlp_head_scan_fits(int p);
-void launch_mlp_head_scan(const HeadScanArgs& a, const FinalizeArgs& fin, hipStream_t s);
 }  // namespace pd

@@ -1,6 +1,7 @@
 // Host runtime of the gfx950 ParaDiGMS library: the C ABI of paradigms.h,
 // argument validation, schedule tables, denoiser weights on the device, the
 // sampling workspace and the two sampler loops.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <exception>
@@ -342,7 +343,8 @@ struct pd_denoiser {
     // gmm2d
     DevBuf means, g_a, g_inv2s2, g_coef;
     // mlp: packed weights, and the powers of two of the split ones
-    DevBuf W[4], bias[4], shift1, wscale[4];
+    DevBuf W[4], bias[4], shift1;
+    float* wscale[4] = {nullptr, nullptr, nullptr, nullptr};   // in W, past the packed weights
     // conv1x1
     DevBuf frags, shift_u, shift_c;
     float b4[4] = {0.f, 0.f, 0.f, 0.f};
@@ -371,7 +373,7 @@ struct pd_denoiser {
 
     LinearArgs mlp_layer(int i) const {
         const int Wd = desc.width;
-        return LinearArgs{W[i].p, wscale[i].as<float>(), bias[i].as<float>(), i == 0 ? shift1.as<float>() : nullptr,
+        return LinearArgs{W[i].p, wscale[i], bias[i].as<float>(), i == 0 ? shift1.as<float>() : nullptr,
                           i == 0 ? (int)D : Wd, i == 3 ? (int)D : Wd};
     }
     // MLP: the first three layers through scratch (scratch_floats of the
@@ -425,24 +427,24 @@ static void pack_mlp(pd_denoiser& d, const float* W1, const float* W2, const flo
     const int Wd = d.desc.width, Din = (int)d.D;
     const float* w[4] = {W1, W2, W3, W4};
     const int n[4] = {Wd, Wd, Wd, Din}, k[4] = {Din, Wd, Wd, Wd};
-    DevBuf raw[4], flag;
-    const int32_t zero = 0;
-    flag.upload(&zero, 1);
-    for (int i = 0; i < 4; ++i) {
-        raw[i].upload(w[i], (size_t)n[i] * k[i]);
-        d.W[i].alloc(packed_linear_floats(n[i], k[i]) * sizeof(float));
-        if (k[i] >= kSplitInputs) d.wscale[i].alloc(sizeof(float) * (size_t)n[i]);
-        launch_pack_linear(raw[i].as<float>(), n[i], k[i], d.W[i].as<float>(), d.wscale[i].as<float>(),
-                           flag.as<int32_t>(), nullptr);
-    }
+    size_t most = 0;
+    for (int i = 0; i < 4; ++i) most = std::max(most, (size_t)n[i] * k[i]);
+    DevBuf raw;                                // one layer's weights, then the flag
+    raw.alloc((most + 1) * sizeof(float));
+    int32_t* flag = raw.as<int32_t>() + most;
     int32_t nonfinite = 0;
-    PD_HIP(hipMemcpy(&nonfinite, flag.p, sizeof nonfinite, hipMemcpyDeviceToHost));
-    if (!nonfinite) return;
-    for (int i = 0; i < 4; ++i) {
-        if (!d.wscale[i].p) continue;
-        d.wscale[i].alloc(0);
-        launch_pack_linear(raw[i].as<float>(), n[i], k[i], d.W[i].as<float>(), nullptr, flag.as<int32_t>(), nullptr);
-    }
+    PD_HIP(hipMemcpy(flag, &nonfinite, sizeof nonfinite, hipMemcpyHostToDevice));
+    auto pack = [&](int i, bool split) {       // copies and launches are ordered on the null stream
+        const size_t packed = packed_linear_floats(n[i], k[i]);
+        d.W[i].alloc((packed + (size_t)n[i]) * sizeof(float));
+        d.wscale[i] = split ? d.W[i].as<float>() + packed : nullptr;
+        PD_HIP(hipMemcpy(raw.p, w[i], (size_t)n[i] * k[i] * sizeof(float), hipMemcpyHostToDevice));
+        launch_pack_linear(raw.as<float>(), n[i], k[i], d.W[i].as<float>(), d.wscale[i], flag, nullptr);
+    };
+    for (int i = 0; i < 4; ++i) pack(i, k[i] >= kSplitInputs);
+    PD_HIP(hipMemcpy(&nonfinite, flag, sizeof nonfinite, hipMemcpyDeviceToHost));
+    for (int i = 0; nonfinite && i < 4; ++i)
+        if (d.wscale[i]) pack(i, false);
     PD_HIP(hipStreamSynchronize(nullptr));     // raw is freed on return
 }
 
@@ -681,7 +683,6 @@ struct pd_workspace {
     DevBuf ring, eps, noise, A, B, zstd, tolv, model_t, state, slot, nrow, partials, scratch;
     DevBuf xt, eps2, model_t_next, nrow2;   // Heun: predictions, second epsilons, n_{i+1}
     DevBuf Rt, St, xprev, eprev;            // multistep: tables; the sequential loop's last step
-    DevBuf head_count;                      // fused MLP head: arrival counters per slab, + 1
     int ring_slots() const { return p + 1 + (s->dpm ? 1 : 0); }
     // mapped, coherent pinned host memory that the kernels write directly:
     // the loop state's host copy and the stride of every iteration
@@ -704,13 +705,6 @@ static void host_mapped(T** host, T** dev, size_t count) {
     std::memset(*host, 0, sizeof(T) * count);
     PD_HIP(hipHostGetDevicePointer(reinterpret_cast<void**>(dev), *host, 0));
 }
-
-// The MLP's last layer runs as the Picard update's prologue (one launch for
-// the layer, the update and the stride) when the drift is the Euler step.
-static bool use_mlp_head(const pd_schedule& s, const pd_denoiser& d, int p) {
-    return d.desc.kind == PD_MODEL_MLP && !s.heun && !s.dpm && mlp_head_scan_fits(p);
-}
-static int head_slabs(int64_t D) { return (int)((D + 15) / 16); }
 
 static void create_workspace(const pd_schedule& s, const pd_denoiser& d, int p, int batch,
                              pd_workspace& w) {
@@ -737,14 +731,7 @@ static void create_workspace(const pd_schedule& s, const pd_denoiser& d, int p, 
     w.state.alloc(sizeof(LoopState));
     w.slot.alloc(sizeof(int32_t) * (size_t)(p + hist));
     w.nrow.alloc(sizeof(int32_t) * (size_t)(p + hist));
-    const bool head = use_mlp_head(s, d, p);
-    int nblk = picard_partial_blocks(d.D, batch);
-    if (head && head_slabs(d.D) > nblk) nblk = head_slabs(d.D);
-    w.partials.alloc(sizeof(float) * (size_t)nblk * p * batch);
-    if (head) {
-        w.head_count.alloc(sizeof(int32_t) * (size_t)(head_slabs(d.D) + 1));
-        PD_HIP(hipMemset(w.head_count.p, 0, w.head_count.bytes));
-    }
+    w.partials.alloc(sizeof(float) * (size_t)picard_partial_blocks(d.D, batch) * p * batch);
     if (s.heun) {
         w.xt.alloc(sizeof(float) * (size_t)p * BD);
         w.eps2.alloc(sizeof(float) * (size_t)p * BD);
@@ -1015,7 +1002,6 @@ extern "C" pd_status pd_sample_picard(const pd_schedule* s, const pd_denoiser* d
                                w.tolv.as<float>(), stop.factor, stop.err_div, s->desc.tol_index_offset,
                                w.model_t.as<int32_t>(), w.h_trace_dev, w.slot.as<int32_t>(),
                                w.nrow.as<int32_t>(), mtn, nrow2, slots, hist, xT, x_out, BD};
-        const bool head = use_mlp_head(*s, *d, pc);
         const RowSrc src{w.ring.as<float>(), w.slot.as<int32_t>(), BD,     batch,
                          pc + hist,          w.nrow.as<int32_t>(), &dst->nrows, d->T_train - 1};
         // The kernels write the loop state into host memory as they go, so
@@ -1059,18 +1045,6 @@ extern "C" pd_status pd_sample_picard(const pd_schedule* s, const pd_denoiser* d
                 tm.mark(-1);
                 for (int it = 0; it < need; ++it) {
                     if (it == need - 1) PD_HIP(hipEventRecord(w.batch_event, st));
-                    if (head) {
-                        // the last layer with the update, error, stride and slide
-                        const HiddenBuf h = d->mlp_trunk(src, w.scratch.as<float>(), st);
-                        tm.mark(CAT_DENOISER);
-                        const HeadScanArgs ha{d->mlp_layer(3), h, src, dst, w.ring.as<float>(),
-                                              w.eps.as<float>(), w.noise.as<float>(), w.A.as<float>(),
-                                              w.B.as<float>(), batch, d->D, w.partials.as<float>(),
-                                              w.head_count.as<int32_t>(), head_slabs(d->D)};
-                        launch_mlp_head_scan(ha, fin, st);
-                        tm.mark(CAT_UPDATE);
-                        continue;
-                    }
                     if (s->heun && d->desc.kind == PD_MODEL_MLP) {
                         // the MLP's last layer also writes every row's Euler prediction
                         const HeunPredictArgs hp{dst, w.ring.as<float>(), w.A.as<float>(),
