@@ -138,15 +138,13 @@ inline EpsOut eps_store(float* y) {
 
 // ---------------------------------------------------------------- kernels
 // rng.hip
-void launch_normals(uint64_t seed, uint32_t rng_stream, int64_t count, const float* scale,
-                    int64_t per_scale, float* out, hipStream_t s);
+void launch_normals(uint64_t seed, uint32_t rng_stream, int64_t count, float* out, hipStream_t s);
 // A sample's up-front draws in one launch: the prior x_0 (counter stream 0, BD
-// values into x0) and, when noise is given, every step's noise (stream 1,
-// noise_count values, value i scaled by scale[i / per_scale]); the values are
-// those of launch_normals with the same streams.  When init is given, the
-// first block also starts the Picard loop (picard_init_body).
-void launch_sample_setup(uint64_t seed, int64_t BD, float* x0, int64_t noise_count,
-                         const float* scale, int64_t per_scale, float* noise,
+// values into x0) and, when noise is given, the noise of T steps (stream 1, BD
+// values each, those of step i times scale[i]); the unscaled values are those of
+// launch_normals with the same streams.  When init is given, the first block
+// also starts the Picard loop (picard_init_body).
+void launch_sample_setup(uint64_t seed, int64_t BD, float* x0, int64_t T, const float* scale, float* noise,
                          const PicardInit* init, hipStream_t s);
 
 // gmm.hip: exact epsilon of an isotropic 2-D Gaussian mixture.
