@@ -429,23 +429,26 @@ static void pack_mlp(pd_denoiser& d, const float* W1, const float* W2, const flo
     const int n[4] = {Wd, Wd, Wd, Din}, k[4] = {Din, Wd, Wd, Wd};
     size_t most = 0;
     for (int i = 0; i < 4; ++i) most = std::max(most, (size_t)n[i] * k[i]);
-    DevBuf raw;                                // one layer's weights, then the flag
-    raw.alloc((most + 1) * sizeof(float));
-    int32_t* flag = raw.as<int32_t>() + most;
+    // one layer's weights, then the flag: in the forward scratch when it is large
+    // enough (an allocation and a free less)
+    DevBuf own;
+    if (d.fwd_scratch.bytes < (most + 1) * sizeof(float)) own.alloc((most + 1) * sizeof(float));
+    float* raw = own.p ? own.as<float>() : d.fwd_scratch.as<float>();
+    int32_t* flag = reinterpret_cast<int32_t*>(raw + most);
     int32_t nonfinite = 0;
     PD_HIP(hipMemcpy(flag, &nonfinite, sizeof nonfinite, hipMemcpyHostToDevice));
     auto pack = [&](int i, bool split) {       // copies and launches are ordered on the null stream
         const size_t packed = packed_linear_floats(n[i], k[i]);
         d.W[i].alloc((packed + (size_t)n[i]) * sizeof(float));
         d.wscale[i] = split ? d.W[i].as<float>() + packed : nullptr;
-        PD_HIP(hipMemcpy(raw.p, w[i], (size_t)n[i] * k[i] * sizeof(float), hipMemcpyHostToDevice));
-        launch_pack_linear(raw.as<float>(), n[i], k[i], d.W[i].as<float>(), d.wscale[i], flag, nullptr);
+        PD_HIP(hipMemcpy(raw, w[i], (size_t)n[i] * k[i] * sizeof(float), hipMemcpyHostToDevice));
+        launch_pack_linear(raw, n[i], k[i], d.W[i].as<float>(), d.wscale[i], flag, nullptr);
     };
     for (int i = 0; i < 4; ++i) pack(i, k[i] >= kSplitInputs);
     PD_HIP(hipMemcpy(&nonfinite, flag, sizeof nonfinite, hipMemcpyDeviceToHost));
     for (int i = 0; nonfinite && i < 4; ++i)
         if (d.wscale[i]) pack(i, false);
-    PD_HIP(hipStreamSynchronize(nullptr));     // raw is freed on return
+    PD_HIP(hipStreamSynchronize(nullptr));     // raw is freed or reused on return
 }
 
 static void create_denoiser(const pd_model_desc& m, const int64_t* shape, int32_t ndim,
@@ -517,9 +520,9 @@ static void create_denoiser(const pd_model_desc& m, const int64_t* shape, int32_
     d.bias[2].upload(w[5], Wd);
     if (m.kind == PD_MODEL_MLP) {
         d.bias[3].upload(w[7], (size_t)Din);
+        d.fwd_scratch.alloc(d.scratch_floats(kForwardRows) * sizeof(float));
         pack_mlp(d, W1, W2, W3, W4);
         d.shift1.upload(sh.data(), sh.size());
-        d.fwd_scratch.alloc(d.scratch_floats(kForwardRows) * sizeof(float));
         PD_HIP(hipEventCreateWithFlags(&d.fwd_done, hipEventDisableTiming));
         return;
     }
@@ -669,7 +672,7 @@ extern "C" pd_status pd_normals(uint64_t seed, uint32_t rng_stream, int64_t coun
         require(count >= 0, "count must be >= 0");
         if (count == 0) return;
         require(out != nullptr, "out must not be NULL");
-        launch_normals(seed, rng_stream, count, nullptr, 1, out, static_cast<hipStream_t>(stream));
+        launch_normals(seed, rng_stream, count, out, static_cast<hipStream_t>(stream));
     });
 }
 
@@ -808,8 +811,7 @@ static pd_workspace* use_workspace(pd_workspace* ws, std::unique_ptr<pd_workspac
 // the Picard loop when init is given
 static void draw_noise(pd_workspace& w, uint64_t seed, const PicardInit* init, hipStream_t st) {
     const int64_t BD = (int64_t)w.batch * w.D;
-    launch_sample_setup(seed, BD, w.ring.as<float>(), (int64_t)w.T * BD, w.zstd.as<float>(), BD,
-                        w.noise.as<float>(), init, st);
+    launch_sample_setup(seed, BD, w.ring.as<float>(), w.T, w.zstd.as<float>(), w.noise.as<float>(), init, st);
 }
 
 static void fill_stats(pd_sample_stats* stats, int iters, int64_t evals, int batch, bool guided,
