@@ -264,7 +264,9 @@ typedef struct pd_sample_stats {
     double finalize_ms;        /* out: summed event time of the finalize launches      */
 } pd_sample_stats;
 /* When one block holds a sample's window (one sample of up to 256 values) the
- * update launch also takes the stride and slides, and finalize_launches is 0.
+ * update launch also takes the stride and slides, and finalize_launches is 0; for
+ * one MLP sample it also runs the next iteration's first layer, where the window
+ * fits (up to 96 points of 256 values, 128 of 160 or fewer).
  * With the 2-D mixture, when the sample's loop state fits in one workgroup, the whole
  * loop (for Picard sampling also the up-front draws) is one launch:
  * update_launches is 1, update_ms times it, and the denoiser and finalize
@@ -274,7 +276,7 @@ typedef struct pd_workspace pd_workspace;
 
 /* Buffers for sampling with window p and batch size `batch` on the current
  * device: the window ring of p+1 points (p+2 for PD_DDIM_DPM2M, which also
- * keeps x_{t-1}), the noise of all T steps, the drift batch and the loop
+ * keeps x_{t-1}; twice for one MLP sample of up to 256 values), the noise of all T steps, the drift batch and the loop
  * state, plus mapped pinned host memory that the kernels write the loop
  * state and the stride of every iteration into (so the host reads them
  * without copies).  Lets repeated calls avoid allocation. */

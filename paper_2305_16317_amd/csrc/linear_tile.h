@@ -147,44 +147,59 @@ __device__ __forceinline__ SplitX split_row(const lin_f4& a, const lin_f4& b, fl
     return s;
 }
 
+// Where a tile's input rows come from.
+enum LinearIn {
+    IN_HIDDEN,     // a hidden buffer of Mmax rows
+    IN_GATHER,     // the window's ring slots or a [rows][D] batch (the first layer)
+    IN_LDS,        // the tile's 16 rows in LDS (the first layer after a scan in the same block)
+};
+struct TileRows {
+    int M, Mmax;               // active rows, and rows of the launch's buffers
+    HiddenBuf in;              // IN_HIDDEN
+    const RowSrc* src;         // IN_GATHER
+    int64_t D;                 // IN_GATHER: values of a row
+    const float* x;            // IN_LDS: row j at x + j xs
+    int xs;
+    const int* n;              // IN_LDS: network timestep of row j
+};
+
 // The tile of row tiles mt0.. and feature tiles nt0..; every thread of the
 // block calls it, and emit(tile, u) is then called for the block's outputs: u
 // the pre-activation of row j = (tid / 4) % 16 and feature 4 g + e, g =
 // (tid / 64) % 4, e = tid % 4, of the 16 x 16 block (row tile mt0 + tile / CT,
 // feature tile nt0 + tile % CT), which is the same for the whole wave (the row
 // or feature may lie past the end: nothing is stored for those).  Returns false, with
-// nothing emitted, when no row of the tile is active.  Input rows: gathered
-// from the window's ring slots or a [rows][D] batch (GATHER), else a hidden
-// buffer of the launch's largest row count.  Rows and inputs past the end are
-// clamped (to the last active row where rows are gathered, else to the last
-// row of the buffer), loaded and count for nothing.
-template <int RT, int CT, bool GATHER, bool SPLIT, class Emit>
-__device__ __forceinline__ bool linear_tile(const LinearArgs& a, const RowSrc& src, const HiddenBuf& in,
-                                            int64_t D, int mt0, int nt0, LinearLds<RT, CT>& lds, Emit&& emit) {
+// nothing emitted, when no row of the tile is active.  Rows and inputs past the
+// end are clamped (to the last active row where rows are gathered, else to the
+// last row of the buffer), loaded and count for nothing.
+template <int RT, int CT, LinearIn IN, bool SPLIT, class Emit>
+__device__ __forceinline__ bool linear_tile(const LinearArgs& a, const TileRows& rows, int mt0, int nt0,
+                                            LinearLds<RT, CT>& lds, Emit&& emit) {
     static_assert(RT == 1 || RT == 2, "the row maxima are shared out over 512 threads");
+    static_assert(IN != IN_LDS || RT == 1, "one row tile in LDS");
+    constexpr bool GATHER = IN == IN_GATHER;
     typedef LinearChunk<RT, CT> Chunk;
     const int tid = threadIdx.x, lane = tid & 63, j = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int groups = src.active ? *src.active : src.max_groups;
-    const int Mmax = src.max_groups * src.group;
+    const int M = rows.M, Mmax = rows.Mmax;
     const int K = a.K, N = a.N, K4 = K / 4;
     const int KC = (K + 31) / 32, NT = (N + 15) / 16;
     // gathered rows need the loop state first: only the active groups' slots
     // are set (past them a slot may never have been written)
-    if constexpr (GATHER) {
-        if (16 * mt0 >= groups * src.group) return false;     // uniform over the block
+    if constexpr (IN != IN_HIDDEN) {
+        if (16 * mt0 >= M) return false;                      // uniform over the block
     }
-    const int Mread = GATHER ? groups * src.group : Mmax;
+    const int Mread = IN == IN_HIDDEN ? Mmax : M;
 
     // the input rows' largest values, read first (loads return in order)
     uint32_t mrow = 0;
-    if constexpr (SPLIT && !GATHER) {
+    if constexpr (SPLIT && IN == IN_HIDDEN) {
         constexpr int PARTS = kLinThreads / (16 * RT);
         const int r = tid % (16 * RT), part = tid / (16 * RT);
         const int row = min(16 * mt0 + r, Mmax - 1), mt = row >> 4;
-        const int NTi = (K + 15) / 16, rows = tile_rows(Mmax, mt);
+        const int NTi = (K + 15) / 16, nr = tile_rows(Mmax, mt);
         for (int n4 = part; n4 < (NTi + 3) / 4; n4 += PARTS) {
-            const lin_u4 v = *reinterpret_cast<const lin_u4*>(in.rmax + rmax_word(NTi, mt, rows, 4 * n4, row & 15));
+            const lin_u4 v = *reinterpret_cast<const lin_u4*>(rows.in.rmax + rmax_word(NTi, mt, nr, 4 * n4, row & 15));
 #pragma unroll
             for (int e = 0; e < 4; ++e) mrow = umax32(mrow, 4 * n4 + e < NTi ? v[e] : 0u);
         }
@@ -197,13 +212,17 @@ __device__ __forceinline__ bool linear_tile(const LinearArgs& a, const RowSrc& s
     for (int rt = 0; rt < RT; ++rt) {
         const int row = min(16 * (mt0 + rt) + j, Mread - 1);
         if constexpr (GATHER) {
+            const RowSrc& src = *rows.src;
             const int gr = row / src.group, b = row % src.group;
             const int64_t sl = src.slot ? src.slot[gr] : gr;
-            xp[rt] = src.base + sl * src.slot_stride + (int64_t)b * D;
+            xp[rt] = src.base + sl * src.slot_stride + (int64_t)b * rows.D;
+            xs[rt] = 4;
+        } else if constexpr (IN == IN_LDS) {
+            xp[rt] = rows.x + j * rows.xs;
             xs[rt] = 4;
         } else {
             const int mt = row >> 4;
-            xp[rt] = in.h + hidden_row(K, mt, row & 15);
+            xp[rt] = rows.in.h + hidden_row(K, mt, row & 15);
             xs[rt] = 4 * tile_rows(Mmax, mt);
         }
     }
@@ -252,17 +271,24 @@ __device__ __forceinline__ bool linear_tile(const LinearArgs& a, const RowSrc& s
         const int tile = min(2 * i + upper, RT * CT - 1);
         const int n = min(16 * (nt0 + tile % CT) + on, N - 1);
         const int row = min(16 * (mt0 + tile / CT) + oj, Mread - 1);
-        addv[i] = GATHER ? a.shift[(int64_t)row_timestep(src, src.group == 1 ? row : row / src.group) * N + n] : a.bias[n];
+        if constexpr (GATHER) {
+            const int gr = rows.src->group == 1 ? row : row / rows.src->group;
+            addv[i] = a.shift[(int64_t)row_timestep(*rows.src, gr) * N + n];
+        } else if constexpr (IN == IN_LDS) {
+            addv[i] = a.shift[(int64_t)rows.n[row - 16 * mt0] * N + n];
+        } else {
+            addv[i] = a.bias[n];
+        }
         wsv[i] = SPLIT ? a.wscale[n] : 1.f;
     }
     // the loads above stay ahead of this exit (they need no loop state)
     asm volatile("" ::: "memory");
-    if (16 * mt0 >= groups * src.group) return false;         // uniform over the block
+    if (16 * mt0 >= M) return false;                          // uniform over the block
 
     float S[RT];
     bool nonfinite = false;
     if constexpr (SPLIT) {
-        if constexpr (GATHER) {
+        if constexpr (IN != IN_HIDDEN) {
             // this wave's chunks of each row, from the registers that hold the
             // first ones (clamped inputs repeat one of the row)
             uint32_t m[RT];
@@ -377,6 +403,38 @@ __device__ __forceinline__ bool linear_tile(const LinearArgs& a, const RowSrc& s
         }
     }
     return true;
+}
+
+// A hidden layer's tile: GELU into the next layer's input layout, and the
+// maximum of each row over each 16-feature tile.
+template <int RT, int CT, LinearIn IN, bool SPLIT>
+__device__ __forceinline__ void hidden_tile(const LinearArgs& a, const TileRows& in, const HiddenBuf& out, int mt0,
+                                            int nt0, LinearLds<RT, CT>& lds) {
+    const int M = in.M, N = a.N;
+    const int j = (threadIdx.x >> 2) & 15, g = (threadIdx.x >> 6) & 3, e = threadIdx.x & 3;
+    const bool any = linear_tile<RT, CT, IN, SPLIT>(a, in, mt0, nt0, lds, [&](int tile, float u) {
+        const float v = gelu_exact(u);
+        const int mt = mt0 + tile / CT, nt = nt0 + tile % CT, rows = tile_rows(in.Mmax, mt);
+        const bool valid = j < M - 16 * mt && 4 * g + e < N - 16 * nt;
+        if (valid) (out.h + hidden_row(N, mt, 0) + (int64_t)nt * 16 * rows)[(g * rows + j) * 4 + e] = v;
+        // largest of the quad's four features
+        uint32_t m = valid ? __builtin_bit_cast(uint32_t, v) & 0x7fffffffu : 0u;
+        m = umax32(m, (uint32_t)__builtin_amdgcn_mov_dpp((int)m, 0xb1, 0xf, 0xf, false));
+        m = umax32(m, (uint32_t)__builtin_amdgcn_mov_dpp((int)m, 0x4e, 0xf, 0xf, false));
+        if (e == 0) lds.pm[tile][g][j] = m;
+    });
+    if (!any) return;
+    lds_barrier();
+    const int NT = (N + 15) / 16;
+    for (int i = threadIdx.x; i < RT * CT * 16; i += kLinThreads) {
+        const int tile = i >> 4, r = i & 15;
+        const int mt = mt0 + tile / CT, nt = nt0 + tile % CT;
+        if (16 * mt + r < M && nt < NT) {
+            const uint32_t m = umax32(umax32(lds.pm[tile][0][r], lds.pm[tile][1][r]),
+                                      umax32(lds.pm[tile][2][r], lds.pm[tile][3][r]));
+            out.rmax[rmax_word(NT, mt, tile_rows(in.Mmax, mt), nt, r)] = m;
+        }
+    }
 }
 
 }  // namespace pd

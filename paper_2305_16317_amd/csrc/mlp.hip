@@ -9,40 +9,16 @@
 namespace pd {
 namespace {
 
-// A hidden layer: GELU of the tile into the next layer's input layout, and the
-// maximum of each row over each 16-feature tile.
-template <int RT, int CT, bool GATHER, bool SPLIT>
+__device__ __forceinline__ TileRows tile_rows_of(const RowSrc& src, const HiddenBuf& in, int64_t D) {
+    return TileRows{(src.active ? *src.active : src.max_groups) * src.group, src.max_groups * src.group, in, &src, D,
+                    nullptr, 0, nullptr};
+}
+
+template <int RT, int CT, LinearIn IN, bool SPLIT>
 __global__ __launch_bounds__(kLinThreads) void k_linear(LinearArgs a, RowSrc src, HiddenBuf in, int64_t D,
                                                         HiddenBuf out) {
     __shared__ LinearLds<RT, CT> lds;
-    const int mt0 = blockIdx.y * RT, nt0 = blockIdx.x * CT;
-    const int Mmax = src.max_groups * src.group, N = a.N;
-    const int M = (src.active ? *src.active : src.max_groups) * src.group;
-    const int j = (threadIdx.x >> 2) & 15, g = (threadIdx.x >> 6) & 3, e = threadIdx.x & 3;
-    const bool any = linear_tile<RT, CT, GATHER, SPLIT>(
-        a, src, in, D, mt0, nt0, lds, [&](int tile, float u) {
-            const float v = gelu_exact(u);
-            const int mt = mt0 + tile / CT, nt = nt0 + tile % CT, rows = tile_rows(Mmax, mt);
-            const bool valid = j < M - 16 * mt && 4 * g + e < N - 16 * nt;
-            if (valid) (out.h + hidden_row(N, mt, 0) + (int64_t)nt * 16 * rows)[(g * rows + j) * 4 + e] = v;
-            // largest of the quad's four features
-            uint32_t m = valid ? __builtin_bit_cast(uint32_t, v) & 0x7fffffffu : 0u;
-            m = umax32(m, (uint32_t)__builtin_amdgcn_mov_dpp((int)m, 0xb1, 0xf, 0xf, false));
-            m = umax32(m, (uint32_t)__builtin_amdgcn_mov_dpp((int)m, 0x4e, 0xf, 0xf, false));
-            if (e == 0) lds.pm[tile][g][j] = m;
-        });
-    if (!any) return;
-    lds_barrier();
-    const int NT = (N + 15) / 16;
-    for (int i = threadIdx.x; i < RT * CT * 16; i += kLinThreads) {
-        const int tile = i >> 4, j = i & 15;
-        const int mt = mt0 + tile / CT, nt = nt0 + tile % CT;
-        if (16 * mt + j < M && nt < NT) {
-            const uint32_t m = umax32(umax32(lds.pm[tile][0][j], lds.pm[tile][1][j]),
-                                      umax32(lds.pm[tile][2][j], lds.pm[tile][3][j]));
-            out.rmax[rmax_word(NT, mt, tile_rows(Mmax, mt), nt, j)] = m;
-        }
-    }
+    hidden_tile<RT, CT, IN, SPLIT>(a, tile_rows_of(src, in, D), out, blockIdx.y * RT, blockIdx.x * CT, lds);
 }
 
 // The last layer: epsilon, row-major, or the step that follows it.  With h,
@@ -52,9 +28,10 @@ __global__ __launch_bounds__(kLinThreads) void k_linear_out(LinearArgs a, RowSrc
                                                             HeunPredictArgs h, EpsOut out) {
     __shared__ LinearLds<RT, CT> lds;
     const int mt0 = blockIdx.y * RT, nt0 = blockIdx.x * CT;
-    const int M = (src.active ? *src.active : src.max_groups) * src.group, N = a.N;
-    linear_tile<RT, CT, false, SPLIT>(
-        a, src, in, 0, mt0, nt0, lds, [&](int tile, float e) {
+    const TileRows rows = tile_rows_of(src, in, 0);
+    const int M = rows.M, N = a.N;
+    linear_tile<RT, CT, IN_HIDDEN, SPLIT>(
+        a, rows, mt0, nt0, lds, [&](int tile, float e) {
             const int row = 16 * (mt0 + tile / CT) + ((threadIdx.x >> 2) & 15);
             const int n = 16 * (nt0 + tile % CT) + 4 * ((threadIdx.x >> 6) & 3) + (threadIdx.x & 3);
             if (row >= M || n >= N) return;
@@ -173,7 +150,7 @@ void check_sizes(const LinearArgs& a) {
     if ((a.K % 4) != 0 || (a.N % 4) != 0) fail(PD_ERR_UNSUPPORTED, "mlp layer sizes must be multiples of 4");
 }
 
-template <bool GATHER>
+template <LinearIn IN>
 void launch_hidden(const LinearArgs& a, const RowSrc& rows, const HiddenBuf& in, int64_t D, const HiddenBuf& out,
                    hipStream_t s) {
     const int64_t M = (int64_t)rows.max_groups * rows.group;
@@ -182,8 +159,8 @@ void launch_hidden(const LinearArgs& a, const RowSrc& rows, const HiddenBuf& in,
     with_tile(M, a.N, [&](auto rt, auto ct, dim3 grid) {
         constexpr int RT = decltype(rt)::value, CT = decltype(ct)::value;
         const dim3 block(kLinThreads);
-        if (a.wscale) hipLaunchKernelGGL((k_linear<RT, CT, GATHER, true>), grid, block, 0, s, a, rows, in, D, out);
-        else hipLaunchKernelGGL((k_linear<RT, CT, GATHER, false>), grid, block, 0, s, a, rows, in, D, out);
+        if (a.wscale) hipLaunchKernelGGL((k_linear<RT, CT, IN, true>), grid, block, 0, s, a, rows, in, D, out);
+        else hipLaunchKernelGGL((k_linear<RT, CT, IN, false>), grid, block, 0, s, a, rows, in, D, out);
     });
     PD_HIP(hipGetLastError());
 }
@@ -223,12 +200,12 @@ void launch_pack_linear(const float* W, int N, int K, float* out, float* wscale,
 }
 
 void launch_linear_first(const LinearArgs& a, const RowSrc& src, int64_t D, const HiddenBuf& out, hipStream_t s) {
-    launch_hidden<true>(a, src, HiddenBuf{}, D, out, s);
+    launch_hidden<IN_GATHER>(a, src, HiddenBuf{}, D, out, s);
 }
 
 void launch_linear_hidden(const LinearArgs& a, const HiddenBuf& in, const RowSrc& rows, const HiddenBuf& out,
                           hipStream_t s) {
-    launch_hidden<false>(a, rows, in, 0, out, s);
+    launch_hidden<IN_HIDDEN>(a, rows, in, 0, out, s);
 }
 
 void launch_linear_out(const LinearArgs& a, const HiddenBuf& in, const RowSrc& rows, const EpsOut& out,

@@ -279,4 +279,27 @@ bool launch_picard_scan(const LoopState* st, float* ring, const float* eps, cons
                         int batch, int64_t D, float* partials, const FinalizeArgs& fin,
                         const float* eps2, hipStream_t s);
 void launch_picard_finalize(const FinalizeArgs& fin, hipStream_t s);
+// Scan, stride and slide of one sample's window and the next iteration's first
+// MLP layer in one launch (picard.hip: k_scan_first).  The old window and state
+// are read from ring_in and st, the new ones written to ring_out and fin.st (other
+// buffers); fin's partials are not used.
+struct ScanFirstArgs {
+    const LoopState* st;
+    const float* ring_in;
+    float* ring_out;
+    const float* eps;       // the drift batch, the history row first for the multistep drift
+    const float* eps2;      // Heun's second evaluations, or nullptr
+    const float* noise;     // [T][D] or nullptr
+    const float* A;
+    const float* B;
+    const float* R;         // multistep coefficients, or nullptr
+    const float* S;
+    int64_t D;
+    int32_t rows_max;       // rows of the layer's buffers: p + history
+    int32_t n_max;          // T_train - 1
+};
+bool scan_first_fits(int p, int batch, int64_t D, const LinearArgs& l1);
+void launch_scan_first(const ScanFirstArgs& a, const FinalizeArgs& fin, const LinearArgs& l1, const HiddenBuf& out,
+                       hipStream_t s);
+
 }  // namespace pd

@@ -102,8 +102,8 @@ __global__ __launch_bounds__(256) void k_heun_predict(const LoopState* __restric
 // model_t_next[t + i] for i < 2p, which covers every index read here (the
 // next window starts at t + stride <= t + p_eff).  Thread 0 rewrites the loop
 // state.
-__device__ void finalize_apply(const FinalizeArgs& a, int stride, int bad, const LoopState& cur,
-                               const int* mt, const int* mt2) {
+__device__ void slide_window(const FinalizeArgs& a, int stride, int bad, const LoopState& cur,
+                             const int* mt, const int* mt2) {
     LoopState* st = a.st;
     const int p = a.p, T = a.T;
     const int t = cur.t, k = cur.k, pe = cur.p_eff, rows_now = cur.nrows;
@@ -140,11 +140,15 @@ __device__ void finalize_apply(const FinalizeArgs& a, int stride, int bad, const
         a.nrow[hn + j] = model_t(m);
         if (a.nrow2) a.nrow2[j] = model_t_next(m);
     }
-    // the iteration that reaches T copies x_T out, so the host needs no copy
-    // launch: its new points are this block's own stores (waited for here) or
-    // were made visible to it by kernel order or the count-in.  The condition
-    // is uniform over the block.
-    if (!bad && tn >= T) {
+}
+
+// The iteration that reaches T copies x_T out, so the host needs no copy launch:
+// its new points are this block's own stores (waited for here) or were made
+// visible to it by kernel order.  The condition is uniform over the block.
+__device__ void finalize_apply(const FinalizeArgs& a, int stride, int bad, const LoopState& cur, const int* mt,
+                               const int* mt2) {
+    slide_window(a, stride, bad, cur, mt, mt2);
+    if (!bad && cur.t + stride >= a.T) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         for (int64_t i = threadIdx.x; i < a.BD; i += blockDim.x) a.x_out[i] = a.xT[i];
@@ -470,6 +474,256 @@ __global__ __launch_bounds__(NW * 64) void k_picard_scan(
 }
 
 
+// The scan, stride and slide of one sample's window, and the first layer of the
+// next iteration, in one launch: every block of the first layer's grid works out
+// the whole update for itself (the same additions in the same order, so the
+// same stride), and takes its 16 rows of the new window from its own registers.
+// Nothing is exchanged between blocks: the old window and the loop state are
+// read from one pair of buffers and the new ones written to the other, each
+// block storing its share of the new points and the first one the rest.
+//
+// Bound by latency, as the launches it replaces were: two round trips for the
+// loop state and the window (at most 128 points of 256 values, 192 KB at 100
+// points of 160), a few barriers, and the tile.  At 100 points of 160 and width
+// 1024 it takes 12.3 us, apart 8.2 and 5.7 and a launch gap of about 1; at 15
+// points 8.2, apart 4.2 and 4.9 and the gap.
+//
+// Threads: C4 = D / 4 column groups of four by row groups of ch consecutive
+// window rows (at least four, so that few totals are added up).
+constexpr int kFusedRows = 128, kFusedCols = 256;
+template <int CT, int R, bool NOISE, bool DPM>
+__global__ __launch_bounds__(kLinThreads) void k_scan_first(ScanFirstArgs s, FinalizeArgs fin, LinearArgs l1,
+                                                            HiddenBuf out) {
+    typedef Cols<4>::type V;
+    __shared__ LinearLds<1, CT> lds;
+    __shared__ V s_ty[kLinThreads], s_tz[kLinThreads];
+    __shared__ float s_d2[kFusedRows][kFusedCols / 4 + 1];
+    __shared__ __attribute__((aligned(16))) float s_x[16][kFusedCols + 4];
+    __shared__ float s_A[kFusedRows], s_B[kFusedRows], s_R[kFusedRows], s_S[kFusedRows], s_err[kFusedRows];
+    __shared__ int s_mt[2 * kFusedRows], s_mt2[2 * kFusedRows], s_n[16];
+    __shared__ int s_wfail[kLinWaves], s_wbad[kLinWaves];
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int bid = blockIdx.x + gridDim.x * blockIdx.y, nb = gridDim.x * gridDim.y;
+    const LoopState cur = *s.st;
+    const int pe = cur.p_eff;
+    if (pe <= 0) {                                   // the loop has ended: pass its state on
+        if (bid == 0 && tid == 0) *fin.st = cur;
+        return;
+    }
+    const int t = cur.t, f = cur.f, P1 = fin.ring_slots, T = fin.T;
+    const int D = (int)s.D, C4 = D / 4;
+    const int groups = kLinThreads / C4;
+    int ch = (pe + groups - 1) / groups;             // <= R: the launch covers a full window
+    ch = ch < 4 ? 4 : ch;
+    const int rg = tid / C4, col = 4 * (tid - rg * C4);
+    const int j0 = min(rg * ch, pe), nr = rg < groups ? min(j0 + ch, pe) - j0 : 0;
+    const int hist = DPM ? cur.nrows - pe : 0;
+    // ring slots by wrapping additions from x_t's
+    const int slot_t = t % P1;
+    auto slot_at = [&](int o) {                      // slot of point t + o, 0 <= o < P1
+        const int v = slot_t + o;
+        return v >= P1 ? v - P1 : v;
+    };
+    auto old_point = [&](int j) {                    // window row j: points past f equal x_f
+        return *reinterpret_cast<const V*>(s.ring_in + (int64_t)slot_at(min(j, f - t)) * D + col);
+    };
+
+    // ---- the window, every load in flight together
+    V anchor = V(0.f), xnext = V(0.f), xp = V(0.f), ep = V(0.f);
+    V xo[R], y[R], z[R], e2[R];
+    if (nr > 0) {
+        anchor = old_point(0);
+        xnext = old_point(min(j0 + nr, pe - 1));
+        if constexpr (DPM) {
+            // the step before row j0 (for the window's first row x_{t-1}; at t = 0
+            // there is none and its coefficients are zero)
+            const int o = t + j0 > 0 ? j0 - 1 : 0;
+            const int sl = o < 0 ? (slot_t == 0 ? P1 - 1 : slot_t - 1) : slot_at(min(o, f - t));
+            xp = *reinterpret_cast<const V*>(s.ring_in + (int64_t)sl * D + col);
+            ep = *reinterpret_cast<const V*>(s.eps + (int64_t)max(j0 - 1 + hist, 0) * D + col);
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (r < ch) {                            // uniform
+                const int j = min(j0 + r, pe - 1);
+                xo[r] = old_point(j);
+                y[r] = *reinterpret_cast<const V*>(s.eps + (int64_t)(j + hist) * D + col);
+                if (s.eps2 != nullptr) e2[r] = *reinterpret_cast<const V*>(s.eps2 + (int64_t)j * D + col);
+                if constexpr (NOISE) z[r] = *reinterpret_cast<const V*>(s.noise + (int64_t)(t + j) * D + col);
+            }
+        }
+    }
+    // the tile's weights are brought near while the scan runs
+    lin_f4 warm[2 * CT];
+#pragma unroll
+    for (int i = 0; i < 2 * CT; ++i) {
+        const int KC = (l1.K + 31) / 32, NT = (l1.N + 15) / 16;
+        const int nt = min((int)blockIdx.x * CT + i / 2, NT - 1);
+        warm[i] = static_cast<const lin_f4*>(l1.w)[((int64_t)nt * KC + min(w, KC - 1)) * 128 + (i & 1) * 64 + lane];
+    }
+    float ftol = 0.f;
+    if (tid < pe) {
+        s_A[tid] = s.A[t + tid];
+        s_B[tid] = s.B[t + tid];
+        if constexpr (DPM) {
+            s_R[tid] = s.R[t + tid];
+            s_S[tid] = s.S[t + tid];
+        }
+        if (tid >= 1) ftol = offset_tol(fin, t, tid);
+    }
+    if (tid < 2 * fin.p && t + tid < T) {
+        s_mt[tid] = fin.model_t[t + tid];
+        if (fin.nrow2) s_mt2[tid] = fin.model_t_next[t + tid];
+    }
+    lds_barrier();
+
+    // ---- drifts replace eps in y; each thread's totals
+    V ty = V(0.f), tz = V(0.f);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        if (r < nr) {
+            const int j = j0 + r;
+            const float ca = s_A[j], cb = s_B[j];
+            float cr = 0.f, cs = 0.f;
+            if constexpr (DPM) {
+                cr = s_R[j];
+                cs = s_S[j];
+            }
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                // Heun: the mean of the two evaluations but at the chain's last step
+                if (s.eps2 != nullptr && t + j + 1 < T) y[r][c] = __fmul_rn(__fadd_rn(y[r][c], e2[r][c]), 0.5f);
+                const float e = y[r][c];
+                float v = drift(ca, xo[r][c], cb, e);
+                if constexpr (DPM) {
+                    const float v2 = __fadd_rn(__fadd_rn(v, __fmul_rn(cr, xp[c])), __fmul_rn(cs, ep[c]));
+                    v = cr != 0.f ? v2 : v;
+                    xp[c] = xo[r][c];
+                    ep[c] = e;
+                }
+                y[r][c] = v;
+                ty[c] = __fadd_rn(ty[c], v);
+                if constexpr (NOISE) tz[c] = __fadd_rn(tz[c], z[r][c]);
+            }
+        }
+    }
+    s_ty[tid] = ty;
+    if constexpr (NOISE) s_tz[tid] = tz;
+    lds_barrier();
+    V py = V(0.f), pz = V(0.f);
+    if (nr > 0)
+        for (int v0 = 0; v0 < rg; v0 += 4) {         // four totals at a time in flight, added in order
+            V a4[4], b4[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int i = min(v0 + u, rg) * C4 + col / 4;
+                a4[u] = s_ty[i];
+                if constexpr (NOISE) b4[u] = s_tz[i];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (v0 + u < rg)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        py[c] = __fadd_rn(py[c], a4[u][c]);
+                        if constexpr (NOISE) pz[c] = __fadd_rn(pz[c], b4[u][c]);
+                    }
+        }
+
+    // ---- new points (in y) and their squared differences
+    V sy = V(0.f), sz = V(0.f);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        if (r < nr) {
+            const int j = j0 + r;
+            const V xold = (r + 1 < R && r + 1 < nr) ? xo[r + 1 < R ? r + 1 : r] : xnext;
+            float acc = 0.f;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                sy[c] = __fadd_rn(sy[c], y[r][c]);
+                if constexpr (NOISE) sz[c] = __fadd_rn(sz[c], z[r][c]);
+                const float v = __fadd_rn(__fadd_rn(anchor[c], __fadd_rn(py[c], sy[c])), __fadd_rn(pz[c], sz[c]));
+                y[r][c] = v;
+                if (j + 1 < pe) {
+                    const float dl = __fsub_rn(v, xold[c]);
+                    acc += dl * dl;
+                } else {
+                    acc += isfinite(v) ? 0.f : 1.f;  // last row: count non-finite points
+                }
+            }
+            s_d2[j][col / 4] = acc;
+        }
+    }
+    lds_barrier();
+    {
+        const int q = tid >> 2, part = tid & 3;      // four threads a row
+        float sum = 0.f;
+        if (q < pe)
+            for (int i = part; i < C4; i += 4) sum += s_d2[q][i];
+        sum = group_sum<4>(sum);
+        if (part == 0 && q < pe) s_err[q + 1 < pe ? q + 1 : 0] = sum;
+    }
+    lds_barrier();
+    {
+        bool fails = false, bad = false;
+        if (tid == 0) {
+            bad = s_err[0] != 0.f;
+        } else if (tid < pe) {
+            const float err = s_err[tid] / fin.err_div;
+            bad = !isfinite(err);
+            fails = !(err <= ftol);
+        }
+        const uint64_t fm = __ballot(fails), bm = __ballot(bad);
+        if (lane == 0) {
+            s_wfail[w] = fm ? w * 64 + __ffsll((unsigned long long)fm) - 1 : pe;
+            s_wbad[w] = bm != 0;
+        }
+    }
+    lds_barrier();
+    int stride = pe, bad = 0;
+#pragma unroll
+    for (int v = 0; v < kLinWaves; ++v) {
+        stride = min(stride, s_wfail[v]);
+        bad |= s_wbad[v];
+    }
+
+    // ---- the new window: rows i are points first + i (the history row first)
+    const int tn = t + stride;
+    const int pn = bad ? 0 : min(fin.p, T - tn);
+    const int hn = (DPM && tn >= 1 && pn > 0) ? 1 : 0;
+    const int M = pn > 0 ? pn + hn : 0, mt0 = blockIdx.y, i0 = 16 * mt0;
+    const int back = stride - hn + i0;               // row i0's point is t + back (>= t)
+    if (rg == 0) {
+        if (bid == 0) *reinterpret_cast<V*>(s.ring_out + (int64_t)slot_t * D + col) = anchor;
+        if (back == 0) *reinterpret_cast<V*>(&s_x[0][col]) = anchor;
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        if (r < nr) {
+            const int j = j0 + r;                    // the point t + j + 1
+            if (j == bid || (j >= nb && j % nb == bid)) *reinterpret_cast<V*>(s.ring_out + (int64_t)slot_at(j + 1) * D + col) = y[r];
+            int i = j + 1 - back;
+            if (i >= 0 && i < 16) *reinterpret_cast<V*>(&s_x[i][col]) = y[r];
+            if (j == pe - 1) {                       // points past the window's last repeat it
+                for (i = max(i + 1, 0); i < 16; ++i) *reinterpret_cast<V*>(&s_x[i][col]) = y[r];
+                if (bid == 0 && !bad && tn >= T) *reinterpret_cast<V*>(fin.x_out + col) = y[r];
+            }
+        }
+    }
+    if (tid < 16) {
+        const int n = i0 + tid < M ? s_mt[back + tid] : 0;
+        s_n[tid] = n < 0 ? 0 : (n > s.n_max ? s.n_max : n);
+    }
+    if (bid == 0) slide_window(fin, stride, bad, cur, s_mt, fin.nrow2 ? s_mt2 : nullptr);
+    lds_barrier();
+#pragma unroll
+    for (int i = 0; i < 2 * CT; ++i) asm volatile("" ::"v"(warm[i]));
+    if (i0 >= M) return;                             // uniform over the block
+    hidden_tile<1, CT, IN_LDS, false>(
+        l1, TileRows{M, s.rows_max, HiddenBuf{}, nullptr, 0, &s_x[0][0], kFusedCols + 4, s_n}, out, mt0,
+        blockIdx.x * CT, lds);
+}
+
 }  // namespace
 
 // A block covers at most 64 lanes x VEC columns.  When the grid takes more
@@ -548,6 +802,41 @@ bool launch_picard_scan(const LoopState* st, float* ring, const float* eps, cons
     if (ch <= 4) PD_SCAN(8, 4)
     PD_SCAN(8, 8)
 #undef PD_SCAN
+}
+
+// Rows of a window of p points that a thread takes; up to twelve fit its registers.
+static int scan_first_rows(int p, int64_t D) {
+    const int groups = kLinThreads / (int)(D / 4);
+    return (p + groups - 1) / groups;
+}
+bool scan_first_fits(int p, int batch, int64_t D, const LinearArgs& l1) {
+    return batch == 1 && p >= 1 && p <= kFusedRows && D >= 4 && D <= kFusedCols && D % 4 == 0 && l1.K == D &&
+           l1.N % 4 == 0 && l1.wscale == nullptr && scan_first_rows(p, D) <= 12;
+}
+
+template <int CT, int R>
+static void launch_scan_first_t(const ScanFirstArgs& a, const FinalizeArgs& fin, const LinearArgs& l1,
+                                const HiddenBuf& out, hipStream_t s) {
+    const dim3 grid((unsigned)((l1.N + 16 * CT - 1) / (16 * CT)), (unsigned)((a.rows_max + 15) / 16)), block(kLinThreads);
+    if (a.R) hipLaunchKernelGGL((k_scan_first<CT, R, false, true>), grid, block, 0, s, a, fin, l1, out);
+    else if (a.noise) hipLaunchKernelGGL((k_scan_first<CT, R, true, false>), grid, block, 0, s, a, fin, l1, out);
+    else hipLaunchKernelGGL((k_scan_first<CT, R, false, false>), grid, block, 0, s, a, fin, l1, out);
+    PD_HIP(hipGetLastError());
+}
+
+void launch_scan_first(const ScanFirstArgs& a, const FinalizeArgs& fin, const LinearArgs& l1, const HiddenBuf& out,
+                       hipStream_t s) {
+    if (!scan_first_fits(fin.p, fin.batch, a.D, l1) || a.rows_max != fin.p + fin.history || (a.R != nullptr) != (fin.history != 0))
+        fail(PD_ERR_UNSUPPORTED, "fused scan and first layer: sizes");
+    if (a.R && (a.noise || a.eps2)) fail(PD_ERR_INVALID_ARG, "the multistep drift is for the noise-free chain");
+    const int ch = scan_first_rows(fin.p, a.D);
+    // one 16 x 16 block per unit while there are units, then two features tiles a block
+    const bool one = (int64_t)((a.rows_max + 15) / 16) * ((l1.N + 15) / 16) <= device_cus();
+#define PD_FUSED(R) return one ? launch_scan_first_t<1, R>(a, fin, l1, out, s) : launch_scan_first_t<2, R>(a, fin, l1, out, s)
+    if (ch <= 4) PD_FUSED(4);
+    if (ch <= 8) PD_FUSED(8);
+    PD_FUSED(12);
+#undef PD_FUSED
 }
 
 void launch_picard_finalize(const FinalizeArgs& fin, hipStream_t s) {

@@ -380,9 +380,14 @@ struct pd_denoiser {
     // largest row count); returns the third layer's output, the last layer's input
     HiddenBuf mlp_trunk(const RowSrc& src, float* scratch, hipStream_t s) const {
         const int64_t rows = (int64_t)src.max_groups * src.group;
+        launch_linear_first(mlp_layer(0), src, D, hidden_buf(scratch, rows, desc.width), s);
+        return mlp_middle(src, scratch, s);
+    }
+    // the second and third layers alone (the first one's output is in scratch)
+    HiddenBuf mlp_middle(const RowSrc& src, float* scratch, hipStream_t s) const {
+        const int64_t rows = (int64_t)src.max_groups * src.group;
         const HiddenBuf h1 = hidden_buf(scratch, rows, desc.width);
         const HiddenBuf h2 = hidden_buf(scratch + hidden_floats(rows, desc.width), rows, desc.width);
-        launch_linear_first(mlp_layer(0), src, D, h1, s);
         launch_linear_hidden(mlp_layer(1), h1, src, h2, s);
         launch_linear_hidden(mlp_layer(2), h2, src, h1, s);
         return h1;
@@ -684,6 +689,7 @@ struct pd_workspace {
     int p = 0, batch = 0, T = 0;
     int64_t D = 0;
     DevBuf ring, eps, noise, A, B, zstd, tolv, model_t, state, slot, nrow, partials, scratch;
+    DevBuf ring2;                           // second window buffer (use_scan_first)
     DevBuf xt, eps2, model_t_next, nrow2;   // Heun: predictions, second epsilons, n_{i+1}
     DevBuf Rt, St, xprev, eprev;            // multistep: tables; the sequential loop's last step
     int ring_slots() const { return p + 1 + (s->dpm ? 1 : 0); }
@@ -709,6 +715,12 @@ static void host_mapped(T** host, T** dev, size_t count) {
     PD_HIP(hipHostGetDevicePointer(reinterpret_cast<void**>(dev), *host, 0));
 }
 
+// One MLP sample whose window fits: the scan of an iteration runs in the launch
+// of the next one's first layer.
+static bool use_scan_first(const pd_denoiser& d, int p, int batch) {
+    return d.desc.kind == PD_MODEL_MLP && scan_first_fits(p, batch, d.D, d.mlp_layer(0));
+}
+
 static void create_workspace(const pd_schedule& s, const pd_denoiser& d, int p, int batch,
                              pd_workspace& w) {
     w.device = current_device();
@@ -725,13 +737,15 @@ static void create_workspace(const pd_schedule& s, const pd_denoiser& d, int p, 
     const int hist = s.dpm ? 1 : 0;
     w.ring.alloc(sizeof(float) * (size_t)(p + 1 + hist) * BD);
     w.eps.alloc(sizeof(float) * (size_t)(p + hist) * BD);
+    // for any window a call may have, so that its path does not depend on the workspace's
+    if (use_scan_first(d, 1, batch)) w.ring2.alloc(w.ring.bytes);
     if (s.has_noise) w.noise.alloc(sizeof(float) * (size_t)s.T * BD);
     w.A.upload(s.A.data(), s.T);
     w.B.upload(s.B.data(), s.T);
     w.zstd.upload(s.noise_std.data(), s.T);
     w.tolv.upload(s.tol_var.data(), s.T);
     w.model_t.upload(s.model_t.data(), s.T);
-    w.state.alloc(sizeof(LoopState));
+    w.state.alloc(2 * sizeof(LoopState));
     w.slot.alloc(sizeof(int32_t) * (size_t)(p + hist));
     w.nrow.alloc(sizeof(int32_t) * (size_t)(p + hist));
     w.partials.alloc(sizeof(float) * (size_t)picard_partial_blocks(d.D, batch) * p * batch);
@@ -996,16 +1010,46 @@ extern "C" pd_status pd_sample_picard(const pd_schedule* s, const pd_denoiser* d
             fill_stats(stats, w.h_state->k, w.h_state->evals, batch, d->guided(), w.h_trace, tm);
             return;
         }
-        const RowSrc src2{w.xt.as<float>(), nullptr, BD, batch, pc, nrow2, &dst->p_eff, d->T_train - 1};
         const int hist = s->dpm ? 1 : 0;     // the multistep drift's row x_{t-1}
         const int slots = pc + 1 + hist;
-        const float* xT = w.ring.as<float>() + (int64_t)(T % slots) * BD;
-        const FinalizeArgs fin{dst, w.h_state_dev, w.partials.as<float>(), pc, batch, d->D, T,
-                               w.tolv.as<float>(), stop.factor, stop.err_div, s->desc.tol_index_offset,
-                               w.model_t.as<int32_t>(), w.h_trace_dev, w.slot.as<int32_t>(),
-                               w.nrow.as<int32_t>(), mtn, nrow2, slots, hist, xT, x_out, BD};
-        const RowSrc src{w.ring.as<float>(), w.slot.as<int32_t>(), BD,     batch,
-                         pc + hist,          w.nrow.as<int32_t>(), &dst->nrows, d->T_train - 1};
+        // the window and the loop state; with the scan in the next iteration's
+        // first launch both move between two buffers (cur is the one in use)
+        const bool scan_first = use_scan_first(*d, pc, batch);
+        float* const rings[2] = {w.ring.as<float>(), scan_first ? w.ring2.as<float>() : w.ring.as<float>()};
+        int cur = 0;
+        bool open = false;                   // an iteration's scan is still to be launched
+        bool begun = false;                  // the next iteration's first layer has been
+        auto fin_of = [&](int c) {
+            return FinalizeArgs{dst + c, w.h_state_dev, w.partials.as<float>(), pc, batch, d->D, T,
+                                w.tolv.as<float>(), stop.factor, stop.err_div, s->desc.tol_index_offset,
+                                w.model_t.as<int32_t>(), w.h_trace_dev, w.slot.as<int32_t>(),
+                                w.nrow.as<int32_t>(), mtn, nrow2, slots, hist,
+                                rings[c] + (int64_t)(T % slots) * BD, x_out, BD};
+        };
+        auto launch_scan = [&] {             // in place, with the stride and the slide
+            const FinalizeArgs fin = fin_of(cur);
+            const bool fused = launch_picard_scan(
+                dst + cur, rings[cur], w.eps.as<float>(), w.noise.as<float>(), w.A.as<float>(), w.B.as<float>(),
+                w.Rt.as<float>(), w.St.as<float>(), pc, batch, d->D, w.partials.as<float>(), fin,
+                s->heun ? w.eps2.as<float>() : nullptr, st);   // Heun: the scan averages
+            tm.mark(CAT_UPDATE);
+            if (!fused) {
+                launch_picard_finalize(fin, st);
+                tm.mark(CAT_FINALIZE);
+            }
+        };
+        auto launch_scan_and_first = [&] {   // into the other buffers, with the next first layer
+            const ScanFirstArgs sa{dst + cur, rings[cur], rings[1 - cur], w.eps.as<float>(),
+                                   s->heun ? w.eps2.as<float>() : nullptr, w.noise.as<float>(), w.A.as<float>(),
+                                   w.B.as<float>(), w.Rt.as<float>(), w.St.as<float>(), d->D, pc + hist,
+                                   d->T_train - 1};
+            cur = 1 - cur;
+            launch_scan_first(sa, fin_of(cur), d->mlp_layer(0),
+                              hidden_buf(w.scratch.as<float>(), pc + hist, d->desc.width), st);
+            tm.mark(CAT_UPDATE);
+            open = false;
+            begun = true;
+        };
         // The kernels write the loop state into host memory as they go, so
         // the host decides each next batch while the GPU still runs the
         // previous batch's last iteration (it waits on an event recorded
@@ -1040,47 +1084,61 @@ extern "C" pd_status pd_sample_picard(const pd_schedule* s, const pd_denoiser* d
                 est = est < issued ? est : issued;
                 need = need > est ? need : est;
             }
+            // the chain's last point (sigma = 0) is held to no change at all and so
+            // takes an iteration of its own: while more than that point is left,
+            // one in flight does not end the loop
+            if (need <= in_flight && T - t_host > 1) need = in_flight + 1;
             need = need < T - t_host ? need : T - t_host;   // stride >= 1 bounds the rest
             need -= in_flight;
             if (issued + need > T) need = T - issued;
             if (need > 0) {
                 tm.mark(-1);
                 for (int it = 0; it < need; ++it) {
-                    if (it == need - 1) PD_HIP(hipEventRecord(w.batch_event, st));
-                    if (s->heun && d->desc.kind == PD_MODEL_MLP) {
-                        // the MLP's last layer also writes every row's Euler prediction
-                        const HeunPredictArgs hp{dst, w.ring.as<float>(), w.A.as<float>(),
-                                                 w.B.as<float>(), slots, w.xt.as<float>()};
-                        launch_linear_out_predict(d->mlp_layer(3),
-                                                  d->mlp_trunk(src, w.scratch.as<float>(), st), src,
-                                                  hp, w.eps.as<float>(), st);
+                    const bool last = it == need - 1;
+                    if (open) launch_scan_and_first();
+                    // every scan but this iteration's own is queued
+                    if (last) PD_HIP(hipEventRecord(w.batch_event, st));
+                    LoopState* const now = dst + cur;
+                    const RowSrc src{rings[cur], w.slot.as<int32_t>(), BD, batch, pc + hist,
+                                     w.nrow.as<int32_t>(), &now->nrows, d->T_train - 1};
+                    if (d->desc.kind == PD_MODEL_MLP) {
+                        const HiddenBuf h = begun ? d->mlp_middle(src, w.scratch.as<float>(), st)
+                                                  : d->mlp_trunk(src, w.scratch.as<float>(), st);
+                        begun = false;
+                        if (s->heun) {       // the last layer also writes every row's Euler prediction
+                            const HeunPredictArgs hp{now, rings[cur], w.A.as<float>(), w.B.as<float>(), slots,
+                                                     w.xt.as<float>()};
+                            launch_linear_out_predict(d->mlp_layer(3), h, src, hp, w.eps.as<float>(), st);
+                        } else {
+                            launch_linear_out(d->mlp_layer(3), h, src, eps_store(w.eps.as<float>()), st);
+                        }
                     } else {
                         d->forward(src, w.eps.as<float>(), w.scratch.as<float>(), st);
                         if (s->heun)
-                            launch_heun_predict(dst, w.ring.as<float>(), w.eps.as<float>(),
-                                                w.A.as<float>(), w.B.as<float>(), pc, BD,
-                                                w.xt.as<float>(), st);
+                            launch_heun_predict(now, rings[cur], w.eps.as<float>(), w.A.as<float>(),
+                                                w.B.as<float>(), pc, BD, w.xt.as<float>(), st);
                     }
                     // Heun: the second evaluation, at every row's Euler prediction
-                    if (s->heun) d->forward(src2, w.eps2.as<float>(), w.scratch.as<float>(), st);
-                    tm.mark(CAT_DENOISER);
-                    const bool fused = launch_picard_scan(
-                        dst, w.ring.as<float>(), w.eps.as<float>(), w.noise.as<float>(),
-                        w.A.as<float>(), w.B.as<float>(), w.Rt.as<float>(), w.St.as<float>(), pc,
-                        batch, d->D, w.partials.as<float>(), fin,
-                        s->heun ? w.eps2.as<float>() : nullptr, st);   // Heun: the scan averages
-                    tm.mark(CAT_UPDATE);
-                    if (!fused) {
-                        launch_picard_finalize(fin, st);
-                        tm.mark(CAT_FINALIZE);
+                    if (s->heun) {
+                        const RowSrc src2{w.xt.as<float>(), nullptr, BD, batch, pc, nrow2, &now->p_eff,
+                                          d->T_train - 1};
+                        d->forward(src2, w.eps2.as<float>(), w.scratch.as<float>(), st);
                     }
+                    tm.mark(CAT_DENOISER);
+                    if (scan_first) open = true;
+                    else launch_scan();
                 }
                 issued += need;
                 // every iteration but the batch's last has run: decide the
                 // next batch while that one runs
                 PD_HIP(hipEventSynchronize(w.batch_event));
             } else if (in_flight > 0) {
-                PD_HIP(hipStreamSynchronize(st));   // the queued ones may finish the loop
+                // the queued ones may finish the loop
+                if (open) {                         // the last one's scan is not queued yet
+                    tm.mark(-1);
+                    launch_scan_and_first();
+                }
+                PD_HIP(hipStreamSynchronize(st));
             } else {
                 fail(PD_ERR_DEVICE, "Picard loop did not terminate within T iterations");
             }

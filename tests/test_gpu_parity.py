@@ -112,6 +112,8 @@ def test_mlp_forward(shape, width, M):
     (24, 516, 1e-3),      # products far below the biases
     (44, 508, 1.0),       # the longest fp32 layer, ragged
     (4, 4, 1.0),          # one chunk, one feature tile, mostly padding
+    (1100, 64, 1.0),      # a split first layer of more chunks than are held at once
+    (520, 516, 1.0),      # split first layer, ragged
 ])
 def test_mlp_tiles_match_float64(D, width, scale):
     """Every tile shape (row counts around its edges), against float64: a float32 evaluation
@@ -511,6 +513,40 @@ def test_prop2_rule_matches_oracle(name, eps):
     ref = Problem(wl, w, np.float32).picard(tau=eps, rule="prop2")
     assert (st.iters, st.trace, st.evals_per_sample) == (ref.iters, ref.trace, ref.evals)
     assert _rel(got, ref.x) <= REL_F32, _rel(got, ref.x)
+
+
+@pytest.mark.parametrize("solver", ["ddpm", "ddim", "noisy", "heun", "dpm2m"])
+@pytest.mark.parametrize("D,width,T,p", [
+    (4, 32, 20, 7),          # one column group; more row groups than rows
+    (16, 40, 60, 17),        # the history row opens a second row tile
+    (160, 32, 40, 40),       # four rows a thread
+    (160, 36, 130, 100),     # nine rows a thread
+    (256, 32, 100, 96),      # the widest window of the fused launch, twelve rows a thread
+    (256, 32, 100, 97),      # past it: scan and first layer apart
+    (260, 32, 30, 16),       # past it by columns
+])
+def test_mlp_one_sample_windows_match_oracle(solver, D, width, T, p):
+    """One MLP sample: the scan runs in the next iteration's first layer where the window fits,
+    else apart; either way K, the strides and the sample are the oracle's, also when the workspace
+    is for a larger window and used again."""
+    kind = "ddpm" if solver == "ddpm" else "ddim"
+    spec = W.ScheduleSpec(kind, T if kind == "ddpm" else 5 * T, T, eta=0.7 if solver == "noisy" else 0.0,
+                          solver=solver if solver in ("heun", "dpm2m") else "euler")
+    m = W.ModelSpec("mlp", (D,), width=width, weight_seed=D)
+    wl = W.Workload("t", spec, m, p=p, tau=0.2, noise_seed=p)
+    w = W.make_weights(m)
+    ref = Problem(wl, w, np.float32).picard()
+    got, st = _run(wl, w)
+    assert (st.iters, st.trace) == (ref.iters, ref.trace)
+    assert st.evals_per_sample == ref.evals
+    assert _rel(got, ref.x) <= REL_F32
+    sched, den = pd.from_workload(wl, w)
+    ws = pd.pd_workspace_create(sched, den, min(T, p + 20), 1)
+    x = torch.empty(D, device="cuda")
+    for _ in range(2):
+        st = pd.pd_sample_picard(sched, den, p, wl.tau, wl.noise_seed, 1, (D,), x, ws)
+        assert st.trace == ref.trace and np.array_equal(x.cpu().numpy(), got[0])
+
 
 
 def test_prop2_rule_is_relaxed_rule_at_matching_tau():
