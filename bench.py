@@ -39,6 +39,15 @@ PEAK = {"f32": 157.3e12, "bf16": 2.5e15, "f16": 2.5e15}   # dense MFMA FLOP/s, M
 HBM_PEAK = 8.0e12                              # bytes/s
 
 
+def scan_runs_first_layer(wl) -> bool:
+    """For one MLP sample whose window fits, the update launch also runs the next
+    iteration's first layer: the denoiser events then time the other three, and
+    all four in a sample's first iteration."""
+    D, p = wl.model.D, min(wl.p, wl.schedule.T)
+    return (wl.model.kind == "mlp" and wl.batch == 1 and D <= 256 and D % 4 == 0 and p <= 128
+            and -(-p // (512 // (D // 4))) <= 12)
+
+
 def flops_per_row(model) -> float:
     """Algorithmic matmul FLOPs of one network row (one full sample)."""
     if model.kind == "conv1x1":
@@ -107,11 +116,11 @@ def denoiser_roofline(wl, dtype: str, fl: float, seconds: float) -> dict:
     """Roofline of the denoiser: the method's FLOPs (``flops_per_row``) over the
     dense peak of the matrix-core instruction that executes them."""
     rate = fl / seconds if seconds > 0 else 0.0
-    if wl.model.kind == "conv1x1" and dtype == "f32":
-        # the fp32 network's layers 2-4 run on v_mfma_f32_16x16x32_f16, three
-        # split products per multiply-add: the method's FLOPs are priced against
-        # the fp16 peak; the products the matrix core executes (three per
-        # FLOP, layers 1 and 4 counted alike) are reported beside it
+    if dtype == "f32" and (wl.model.kind == "conv1x1" or (wl.model.kind == "mlp" and wl.model.width >= 512)):
+        # layers 2-4 of the fp32 networks (of an MLP from 512 inputs up) run on
+        # v_mfma_f32_16x16x32_f16, three split products per multiply-add: the
+        # method's FLOPs are priced against the fp16 peak; the products the matrix
+        # core executes (three per FLOP, every layer counted alike) are reported beside it
         ach = SPLIT_PRODUCTS * rate
         return {"bound": "mfma", "achieved": rate / 1e12, "peak": PEAK["f16"] / 1e12,
                 "unit": "TFLOP/s", "frac": rate / PEAK["f16"], "peak_dtype": "f16",
@@ -125,8 +134,9 @@ def denoiser_roofline(wl, dtype: str, fl: float, seconds: float) -> dict:
             "flops": "method"}
 
 
-KERNEL_SOURCES = {"k_conv": ["conv.hip"], "k_picard": ["picard.hip", "linear_tile.h"],
-                  "k_linear": ["mlp.hip", "linear_tile.h"],
+KERNEL_SOURCES = {"k_conv": ["conv.hip", "eps_out.h"], "k_picard": ["picard.hip", "linear_tile.h"],
+                  "k_scan_first": ["picard.hip", "linear_tile.h"],
+                  "k_linear": ["mlp.hip", "linear_tile.h", "eps_out.h"],
                   "k_gmm": ["gmm.hip", "gmm.h", "philox.h"], "k_normals": ["rng.hip", "philox.h"],
                   "k_sample_setup": ["rng.hip", "philox.h"]}
 
@@ -344,6 +354,10 @@ def main() -> int:
     points = sum(window_points(st.trace, wl.p, wl.schedule.T) for st in stats)
     hist = (sum(history_rows(st.trace, wl.schedule.T) for st in stats)
             if getattr(wl.schedule, "solver", "euler") == "dpm2m" else 0)
+    fused = scan_runs_first_layer(wl)
+    heun = getattr(wl.schedule, "solver", "euler") == "heun"
+    if fused:
+        fl -= 2.0 * wl.model.D * wl.model.width * (points + hist - a.steps * min(wl.p, wl.schedule.T))
     ub = update_bytes(wl, points, has_noise, hist)
     upd_rate = ub / (upd_ms * 1e-3) if upd_ms > 0 else 0.0
     kname = denoiser_kernel(wl, dtype)
@@ -372,13 +386,14 @@ def main() -> int:
         "roofline": {**denoiser_roofline(wl, dtype, fl, den_ms * 1e-3),
                      "traffic": traffic, "kernel": kname,
                      # the MLP's layer launches are timed together, as one call
-                     "kernels_per_call": 4 if wl.model.kind == "mlp" else 1,
+                     "kernels_per_call": ((3 if fused else 4) + (4 if heun else 0)) if wl.model.kind == "mlp" else 1,
+                     **({"first_layer": "in the update launch (k_scan_first)"} if fused else {}),
                      "flops_per_launch": fl / max(den_n, 1),
                      "mean_launch_ms": den_ms / max(den_n, 1), "launches": den_n},
         "roofline_update": {"bound": "hbm", "achieved": upd_rate / 1e9, "peak": HBM_PEAK / 1e9,
                             "unit": "GB/s", "frac": upd_rate / HBM_PEAK,
-                            "traffic": traffic_from_profiles(wl.name, "k_picard_scan"),
-                            "kernel": "k_picard_scan",
+                            "traffic": traffic_from_profiles(wl.name, "k_scan_first" if fused else "k_picard_scan"),
+                            "kernel": "k_scan_first" if fused else "k_picard_scan",
                             "bytes_per_launch": ub / max(upd_n, 1),
                             "mean_launch_us": 1e3 * upd_ms / max(upd_n, 1), "launches": upd_n,
                             "finalize_mean_us": 1e3 * fin_ms / max(upd_n, 1)},

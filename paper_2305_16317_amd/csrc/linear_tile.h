@@ -1,7 +1,7 @@
 // One output tile of a dense layer y = act(x W^T + bias) (or + shift[n_row]
 // for the first layer, which carries b1 + e_n) of the synthetic MLP denoiser.
-// Shared by the layer kernels (mlp.hip) and the fused last layer and Picard
-// update (picard.hip).
+// Shared by the layer kernels (mlp.hip) and the Picard update with the next
+// iteration's first layer (picard.hip).
 //
 // Layers are computed transposed, out^T = W x^T: the MFMA's M dimension is the
 // output feature and its N dimension the row.  A tile is RT x CT blocks of
