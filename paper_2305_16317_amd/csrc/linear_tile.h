@@ -137,7 +137,8 @@ __device__ __forceinline__ SplitX split_row(const lin_f4& a, const lin_f4& b, fl
     s.x0 = s.x0s * (_Float16)0.00048828125f;
     if (nonfinite) {
         // an infinite or NaN input keeps its leading part only, so that its
-        // products are those of the value itself
+        // products are those of the value itself (a weight's leading part is
+        // zero only where the weight is)
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             const uint32_t bits = (p0[i >> 1] >> (16 * (i & 1))) & 0x7fff;
@@ -318,22 +319,53 @@ __device__ __forceinline__ bool linear_tile(const LinearArgs& a, const TileRows&
             if (lane < 16 * RT) lds.mx[wave][lane] = mrow;
         }
         lds_barrier();
+        uint32_t m[RT];
+        auto all_waves = [&] {
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) {
+                m[rt] = lds.mx[0][16 * rt + j];
+#pragma unroll
+                for (int v = 1; v < kLinWaves; ++v) m[rt] = umax32(m[rt], lds.mx[v][16 * rt + j]);
+                nonfinite |= m[rt] >= 0x7f800000u;
+            }
+        };
+        all_waves();
+        nonfinite = __ballot(nonfinite) != 0;                 // the same in every wave
+        if (nonfinite) {
+            // rare: the inputs are read once more for the largest finite value
+            // of each row, which scales the finite ones beside a non-finite one
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) m[rt] = 0;
+            for (int c = c_begin; c < c_end; ++c) {
+                const Chunk ch = load(c);
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        const uint32_t v = __builtin_bit_cast(uint32_t, (float)ch.x[rt][u / 4][u % 4]) & 0x7fffffffu;
+                        m[rt] = umax32(m[rt], v < 0x7f800000u ? v : 0u);
+                    }
+            }
+            lds_barrier();                                    // every wave has read the maxima
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) {
+                m[rt] = umax32(m[rt], __shfl_xor(m[rt], 16, 64));
+                m[rt] = umax32(m[rt], __shfl_xor(m[rt], 32, 64));
+                if (g == 0) lds.mx[wave][16 * rt + j] = m[rt];
+            }
+            lds_barrier();
+            all_waves();
+        }
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
-            uint32_t m = lds.mx[0][16 * rt + j];
-#pragma unroll
-            for (int v = 1; v < kLinWaves; ++v) m = umax32(m, lds.mx[v][16 * rt + j]);
-            // S = 2^(14 - e), e the exponent of the largest value; a zero row
-            // takes 1, and so does a row with a non-finite value
-            int e = 14;
-            if (m >= 0x7f800000u) nonfinite = true;
-            else if (m > 0) e = (int)(m >> 23) - 127;
+            // S = 2^(14 - e), e the exponent of the largest finite value; a row
+            // of zeros takes 1
+            int e = m[rt] > 0 ? (int)(m[rt] >> 23) - 127 : 14;
             e = e < -100 ? -100 : e;
             S[rt] = __builtin_bit_cast(float, (uint32_t)(14 - e + 127) << 23);
             // 1 / S = 2^(e - 14), normal for every e above
             if (wave == 0 && g == 0) lds.inv[16 * rt + j] = __builtin_bit_cast(float, (uint32_t)(e - 14 + 127) << 23);
         }
-        nonfinite = __ballot(nonfinite) != 0;
     }
 
     lin_f4 acc[RT][CT];

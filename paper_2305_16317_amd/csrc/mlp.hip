@@ -109,6 +109,9 @@ __global__ __launch_bounds__(256) void k_pack_linear(const float* __restrict__ W
             for (int u = 0; u < 8; ++u) {
                 const float s = w[u] * f1 * f2;
                 p0[u] = (_Float16)s;
+                // zero only where the weight is, for its products with infinities
+                // (the second part takes the difference back)
+                if (p0[u] == (_Float16)0.f && w[u] != 0.f) p0[u] = (_Float16)__builtin_copysignf(0x1p-24f, w[u]);
                 p1[u] = (_Float16)((s - (float)p0[u]) * 2048.f);
             }
             reinterpret_cast<lin_h8*>(dst)[(c * 2) * 64 + lane] = p0;

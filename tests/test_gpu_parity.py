@@ -166,6 +166,44 @@ def test_mlp_non_finite_weights_and_rows(layer):
     assert not np.isfinite(got[7]).any() and np.array_equal(got[keep], clean[keep])
 
 
+def _value_class(a):
+    return np.where(np.isnan(a), 2, np.where(np.isinf(a), np.sign(a), 0)).astype(int)
+
+
+@pytest.mark.parametrize("layer", ["first", "last"])
+def test_mlp_split_layers_propagate_non_finite_values_as_float32(layer):
+    """A row with an infinite or NaN input of a split layer (512 inputs) gives the infinities and NaN
+    that a float32 evaluation gives: also beside finite inputs far above fp16's range, for weights
+    far below their feature's largest, and NaN only where the weight is zero."""
+    rng = np.random.default_rng(5)
+    if layer == "last":
+        # row 7: feature 5 of the third layer overflows, the others stay near 1e34
+        wl = _wl("mlp", (20,), 512)
+        w = W.make_weights(wl.model)
+        w["W3"][5] = np.abs(w["W3"][5]) * np.float32(3e4)
+        w["W4"][:, 5] = np.array([1, -1, 1e-3, -1e-3, 1e-12, -1e-12, 1e-30, -1e-30, 0.0, 1e-42] * 2, np.float32)
+        x = rng.standard_normal((40, 20)).astype(np.float32)
+        x[7] *= np.float32(1e34)
+    else:
+        # every pre-activation is +inf; weights from 1 down to the smallest float
+        wl = _wl("mlp", (512,), 64)
+        w = {k: np.abs(v) for k, v in W.make_weights(wl.model).items()}
+        w["W1"][:, 3] = np.geomspace(1, 1e-38, 64).astype(np.float32)
+        w["W1"][5, 3] = np.float32(1e-45)
+        x = rng.standard_normal((40, 512)).astype(np.float32)
+        x[7] *= np.float32(1e6)
+        x[7, 3] = np.inf
+    x[9, 2] = np.nan
+    n = rng.integers(0, 100, 40).astype(np.int32)
+    got = _forward(wl, w, x, n)
+    with np.errstate(all="ignore"):
+        ref = _oracle_eps(wl, w, x, n)
+    keep = ~np.isin(np.arange(40), [7, 9])
+    assert np.isfinite(ref[keep]).all() and _rel(got[keep], ref[keep]) <= REL_F32
+    assert (_value_class(ref[7]) == 1).sum() >= 8 and np.isnan(ref[9]).all()
+    assert np.array_equal(_value_class(got), _value_class(ref)), (got[7], ref[7])
+
+
 @pytest.mark.parametrize("shape,width,M,cond", [
     ((4, 8, 8), 32, 3, 0),        # two full pixel tiles per row
     ((4, 6, 7), 64, 5, 0),        # ragged last tile (42 pixels)
