@@ -101,7 +101,7 @@ template <int RT, int CT>
 struct LinearLds {
     float part[kLinWaves][RT * CT][256];
     uint32_t mx[kLinWaves][16 * RT];
-    float inv[16 * RT];                    // 1 / S of the tile's rows
+    int xexp[16 * RT];                     // 1 / S = 2^xexp of the tile's rows
     uint32_t pm[RT * CT][4][16];           // maxima of the tile's outputs, per 4 features
 };
 
@@ -262,7 +262,8 @@ __device__ __forceinline__ bool linear_tile(const LinearArgs& a, const TileRows&
 
     // epilogue operands, fetched before the products
     constexpr int E = (RT * CT * 256 + kLinThreads - 1) / kLinThreads;   // outputs per thread
-    float addv[E], wsv[E];
+    float addv[E];
+    int wev[E];
     // the 16 x 16 block of a thread's i-th output is the same for its whole
     // wave: kept in scalar registers, with all addresses that follow from it
     const int upper = __builtin_amdgcn_readfirstlane(tid >> 8);
@@ -280,7 +281,7 @@ __device__ __forceinline__ bool linear_tile(const LinearArgs& a, const TileRows&
         } else {
             addv[i] = a.bias[n];
         }
-        wsv[i] = SPLIT ? a.wscale[n] : 1.f;
+        wev[i] = SPLIT ? a.wexp[n] : 0;
     }
     // the loads above stay ahead of this exit (they need no loop state)
     asm volatile("" ::: "memory");
@@ -361,10 +362,9 @@ __device__ __forceinline__ bool linear_tile(const LinearArgs& a, const TileRows&
             // S = 2^(14 - e), e the exponent of the largest finite value; a row
             // of zeros takes 1
             int e = m[rt] > 0 ? (int)(m[rt] >> 23) - 127 : 14;
-            e = e < -100 ? -100 : e;
+            e = e < -112 ? -112 : e;                          // S at most 2^126
             S[rt] = __builtin_bit_cast(float, (uint32_t)(14 - e + 127) << 23);
-            // 1 / S = 2^(e - 14), normal for every e above
-            if (wave == 0 && g == 0) lds.inv[16 * rt + j] = __builtin_bit_cast(float, (uint32_t)(e - 14 + 127) << 23);
+            if (wave == 0 && g == 0) lds.xexp[16 * rt + j] = e - 14;
         }
     }
 
@@ -430,8 +430,9 @@ __device__ __forceinline__ bool linear_tile(const LinearArgs& a, const TileRows&
             float sum = lds.part[0][tile][o];
 #pragma unroll
             for (int v = 1; v < kLinWaves; ++v) sum += lds.part[v][tile][o];
-            const float u = SPLIT ? __builtin_fmaf(sum * lds.inv[16 * (tile / CT) + oj], wsv[i], addv[i]) : sum + addv[i];
-            emit(tile, u);
+            // both scales at once: one of them alone may leave the float range
+            if constexpr (SPLIT) sum = __builtin_ldexpf(sum, lds.xexp[16 * (tile / CT) + oj] + wev[i]);
+            emit(tile, sum + addv[i]);
         }
     }
     return true;

@@ -51,13 +51,13 @@ __global__ __launch_bounds__(kLinThreads) void k_linear_out(LinearArgs a, RowSrc
 }
 
 // Weights [N][K] -> packed fragments (layout in linear_tile.h), one block per
-// 16 features; with `split`, also each feature's power of two.  *nonfinite is
+// 16 features; with `split`, also the exponent of each feature's power of two.  *nonfinite is
 // set when a weight is infinite or NaN.  Bound by the latency of its loads: whole
 // rows in 16-byte pieces, several in flight, 11 us for a layer of 1024 x 1024.
 // Creating a 160-1024-1024-1024-160 denoiser takes 1.39 ms, 1.43 with single
 // floats 4 KB apart, and the copies alone 1.32.
 __global__ __launch_bounds__(256) void k_pack_linear(const float* __restrict__ W, int N, int K, int split,
-                                                     float* __restrict__ out, float* __restrict__ wscale,
+                                                     float* __restrict__ out, int32_t* __restrict__ wexp,
                                                      int32_t* nonfinite) {
     __shared__ uint32_t s_max[16];
     const int nt = blockIdx.x, tid = threadIdx.x, i = tid & 15;
@@ -88,7 +88,7 @@ __global__ __launch_bounds__(256) void k_pack_linear(const float* __restrict__ W
     // (2^-e alone may exceed the float range)
     const float f1 = __builtin_bit_cast(float, (uint32_t)(-(e / 2) + 127) << 23);
     const float f2 = __builtin_bit_cast(float, (uint32_t)(-(e - e / 2) + 127) << 23);
-    if (split && tid < 16 && n < N) wscale[n] = __builtin_bit_cast(float, (uint32_t)(e + 127) << 23);
+    if (split && tid < 16 && n < N) wexp[n] = e;
     const int KC = (K + 31) / 32;
     float* dst = out + (int64_t)nt * KC * 512;   // 2 KB per chunk
     // thread: feature i, inputs 32 c + 16 (u / 4) + 4 g + u % 4 of lane i + 16 g
@@ -179,7 +179,7 @@ void launch_hidden(const LinearArgs& a, const RowSrc& rows, const HiddenBuf& in,
     with_tile(M, a.N, [&](auto rt, auto ct, dim3 grid) {
         constexpr int RT = decltype(rt)::value, CT = decltype(ct)::value;
         const dim3 block(kLinThreads);
-        if (a.wscale) hipLaunchKernelGGL((k_linear<RT, CT, IN, true>), grid, block, 0, s, a, rows, in, D, out);
+        if (a.wexp) hipLaunchKernelGGL((k_linear<RT, CT, IN, true>), grid, block, 0, s, a, rows, in, D, out);
         else hipLaunchKernelGGL((k_linear<RT, CT, IN, false>), grid, block, 0, s, a, rows, in, D, out);
     });
     PD_HIP(hipGetLastError());
@@ -194,7 +194,7 @@ void launch_out(const LinearArgs& a, const HiddenBuf& in, const RowSrc& rows, co
     with_tile(M, a.N, [&](auto rt, auto ct, dim3 grid) {
         constexpr int RT = decltype(rt)::value, CT = decltype(ct)::value;
         const dim3 block(kLinThreads);
-        if (a.wscale) hipLaunchKernelGGL((k_linear_out<RT, CT, true, PREDICT>), grid, block, 0, s, a, rows, in, h, out);
+        if (a.wexp) hipLaunchKernelGGL((k_linear_out<RT, CT, true, PREDICT>), grid, block, 0, s, a, rows, in, h, out);
         else hipLaunchKernelGGL((k_linear_out<RT, CT, false, PREDICT>), grid, block, 0, s, a, rows, in, h, out);
     });
     PD_HIP(hipGetLastError());
@@ -212,10 +212,10 @@ HiddenBuf hidden_buf(float* p, int64_t rows, int width) {
 
 size_t packed_linear_floats(int N, int K) { return (size_t)((N + 15) / 16) * ((K + 31) / 32) * 512; }
 
-void launch_pack_linear(const float* W, int N, int K, float* out, float* wscale, int32_t* nonfinite,
+void launch_pack_linear(const float* W, int N, int K, float* out, int32_t* wexp, int32_t* nonfinite,
                         hipStream_t s) {
-    hipLaunchKernelGGL(k_pack_linear, dim3((unsigned)((N + 15) / 16)), dim3(256), 0, s, W, N, K, wscale ? 1 : 0, out,
-                       wscale, nonfinite);
+    hipLaunchKernelGGL(k_pack_linear, dim3((unsigned)((N + 15) / 16)), dim3(256), 0, s, W, N, K, wexp ? 1 : 0, out,
+                       wexp, nonfinite);
     PD_HIP(hipGetLastError());
 }
 

@@ -182,8 +182,8 @@ void launch_gmm_sequential_loop(const GmmLoopArgs& a, hipStream_t s);
 // mlp.hip: y = act(x W^T + bias [+ shift[n_row]]) on the matrix cores.
 struct LinearArgs {
     const void* w;        // packed weights (layout in linear_tile.h)
-    const float* wscale;  // [N] power of two of each feature's split weights, or
-                          // nullptr: fp32 weights
+    const int32_t* wexp;  // [N] exponent of each feature's power of two (split weights),
+                          // or nullptr: fp32 weights
     const float* bias;    // [N] (ignored when shift != nullptr)
     const float* shift;   // [T_train][N] per-timestep shift, or nullptr
     int32_t K, N;
@@ -197,9 +197,9 @@ struct HiddenBuf {
 size_t hidden_floats(int64_t rows, int width);           // floats of one buffer (a multiple of 4)
 HiddenBuf hidden_buf(float* p, int64_t rows, int width);
 size_t packed_linear_floats(int N, int K);
-// W [N][K] (device) -> out; split into fp16 parts when wscale is given.
+// W [N][K] (device) -> out; split into fp16 parts when wexp is given.
 // *nonfinite (device) is set when a weight is infinite or NaN.
-void launch_pack_linear(const float* W, int N, int K, float* out, float* wscale, int32_t* nonfinite,
+void launch_pack_linear(const float* W, int N, int K, float* out, int32_t* wexp, int32_t* nonfinite,
                         hipStream_t s);
 // first layer (rows gathered from `src`, fp32 weights), a hidden layer, and the
 // last layer (no activation, row-major output).  Buffers are those of

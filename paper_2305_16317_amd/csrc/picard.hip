@@ -811,7 +811,7 @@ static int scan_first_rows(int p, int64_t D) {
 }
 bool scan_first_fits(int p, int batch, int64_t D, const LinearArgs& l1) {
     return batch == 1 && p >= 1 && p <= kFusedRows && D >= 4 && D <= kFusedCols && D % 4 == 0 && l1.K == D &&
-           l1.N % 4 == 0 && l1.wscale == nullptr && scan_first_rows(p, D) <= 12;
+           l1.N % 4 == 0 && l1.wexp == nullptr && scan_first_rows(p, D) <= 12;
 }
 
 template <int CT, int R>

@@ -342,9 +342,9 @@ struct pd_denoiser {
     int C = 0, T_train = 0, device = 0;
     // gmm2d
     DevBuf means, g_a, g_inv2s2, g_coef;
-    // mlp: packed weights, and the powers of two of the split ones
+    // mlp: packed weights, and the exponents of the split ones
     DevBuf W[4], bias[4], shift1;
-    float* wscale[4] = {nullptr, nullptr, nullptr, nullptr};   // in W, past the packed weights
+    int32_t* wexp[4] = {nullptr, nullptr, nullptr, nullptr};   // in W, past the packed weights
     // conv1x1
     DevBuf frags, shift_u, shift_c;
     float b4[4] = {0.f, 0.f, 0.f, 0.f};
@@ -373,7 +373,7 @@ struct pd_denoiser {
 
     LinearArgs mlp_layer(int i) const {
         const int Wd = desc.width;
-        return LinearArgs{W[i].p, wscale[i], bias[i].as<float>(), i == 0 ? shift1.as<float>() : nullptr,
+        return LinearArgs{W[i].p, wexp[i], bias[i].as<float>(), i == 0 ? shift1.as<float>() : nullptr,
                           i == 0 ? (int)D : Wd, i == 3 ? (int)D : Wd};
     }
     // MLP: the first three layers through scratch (scratch_floats of the
@@ -445,14 +445,14 @@ static void pack_mlp(pd_denoiser& d, const float* W1, const float* W2, const flo
     auto pack = [&](int i, bool split) {       // copies and launches are ordered on the null stream
         const size_t packed = packed_linear_floats(n[i], k[i]);
         d.W[i].alloc((packed + (size_t)n[i]) * sizeof(float));
-        d.wscale[i] = split ? d.W[i].as<float>() + packed : nullptr;
+        d.wexp[i] = split ? d.W[i].as<int32_t>() + packed : nullptr;
         PD_HIP(hipMemcpy(raw, w[i], (size_t)n[i] * k[i] * sizeof(float), hipMemcpyHostToDevice));
-        launch_pack_linear(raw, n[i], k[i], d.W[i].as<float>(), d.wscale[i], flag, nullptr);
+        launch_pack_linear(raw, n[i], k[i], d.W[i].as<float>(), d.wexp[i], flag, nullptr);
     };
     for (int i = 0; i < 4; ++i) pack(i, k[i] >= kSplitInputs);
     PD_HIP(hipMemcpy(&nonfinite, flag, sizeof nonfinite, hipMemcpyDeviceToHost));
     for (int i = 0; nonfinite && i < 4; ++i)
-        if (d.wscale[i]) pack(i, false);
+        if (d.wexp[i]) pack(i, false);
     PD_HIP(hipStreamSynchronize(nullptr));     // raw is freed or reused on return
 }
 

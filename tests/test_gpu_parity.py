@@ -204,6 +204,28 @@ def test_mlp_split_layers_propagate_non_finite_values_as_float32(layer):
     assert np.array_equal(_value_class(got), _value_class(ref)), (got[7], ref[7])
 
 
+@pytest.mark.parametrize("scales", [
+    (1e18, 1e18, 1e-3, 1e-30),    # second layer: inputs near 1e37, results near 1e35
+    (1.0, 1.0, 1e-38, 3e37),      # third layer: inputs near 2e-37, from weights below the normal range
+])
+def test_mlp_split_layers_keep_float32_range(scales):
+    """Split layers (512 inputs) with inputs at both ends of the float range, where float32 sums are
+    as exact as anywhere: products of two 22-bit parts leave 2^-22 each, averaged over 512 (the
+    1e-6 of the other sizes covers it)."""
+    wl = _wl("mlp", (20,), 512)
+    w = W.make_weights(wl.model)
+    sx, s1, s2, s3 = (np.float32(s) for s in scales)
+    w["W1"], w["W2"], w["W3"] = np.abs(w["W1"]) * s1, np.abs(w["W2"]) * s2, w["W3"] * s3
+    w["b2"] = np.zeros_like(w["b2"])
+    rng = np.random.default_rng(8)
+    x = np.abs(rng.standard_normal((40, 20)).astype(np.float32)) * sx
+    n = rng.integers(0, 100, 40).astype(np.int32)
+    tb = schedule.from_spec(wl.schedule)
+    ref = denoisers.Denoiser(wl.model, w, tb.alphabar, np.float64, False)(x.astype(np.float64), n)
+    got = _forward(wl, w, x, n)
+    assert _rel(got, ref) <= 1e-6, _rel(got, ref)
+
+
 @pytest.mark.parametrize("shape,width,M,cond", [
     ((4, 8, 8), 32, 3, 0),        # two full pixel tiles per row
     ((4, 6, 7), 64, 5, 0),        # ragged last tile (42 pixels)
