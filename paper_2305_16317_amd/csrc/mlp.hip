@@ -71,8 +71,10 @@ __global__ __launch_bounds__(256) void k_pack_linear(const float* __restrict__ W
 #pragma unroll 8
             for (int k4 = i; k4 < K / 4; k4 += 16) {
                 const lin_f4 v = row[k4];
+                // the conversion matters: of a vector's element itself bit_cast reads
+                // the vector's first
 #pragma unroll
-                for (int u = 0; u < 4; ++u) mr = umax32(mr, __builtin_bit_cast(uint32_t, v[u]) & 0x7fffffffu);
+                for (int u = 0; u < 4; ++u) mr = umax32(mr, __builtin_bit_cast(uint32_t, (float)v[u]) & 0x7fffffffu);
             }
         }
 #pragma unroll

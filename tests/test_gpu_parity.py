@@ -170,6 +170,27 @@ def _value_class(a):
     return np.where(np.isnan(a), 2, np.where(np.isinf(a), np.sign(a), 0)).astype(int)
 
 
+@pytest.mark.parametrize("k", range(8))
+def test_mlp_packing_reads_every_weight(k):
+    """The largest weight of a split layer's feature, and an infinite one, are found at every position
+    of a lane's eight.  One weight 2^18 times the others (its input is zero, so that the others decide
+    the result) leaves those 2^-37 / 2^-18 exact, below the bar; an infinite weight gives what a
+    float32 evaluation gives."""
+    wl = _wl("mlp", (512,), 64)
+    w = W.make_weights(wl.model)
+    w["W1"][:, 64 + k] = np.float32(2.0 ** 14)
+    x = np.random.default_rng(k).standard_normal((20, 512)).astype(np.float32)
+    x[:, 64 + k] = 0.0
+    n = np.arange(20, dtype=np.int32)
+    got, ref = _forward(wl, w, x, n), _oracle_eps(wl, w, x, n)
+    assert _rel(got, ref) <= REL_F32, _rel(got, ref)
+    wl = _wl("mlp", (20,), 512)
+    w = W.make_weights(wl.model)
+    w["W4"][3, 64 + k] = np.inf
+    got, ref = _forward(wl, w, x[:, :20], n), _oracle_eps(wl, w, x[:, :20], n)
+    assert np.isinf(ref[:, 3]).all() and np.array_equal(got[:, 3], ref[:, 3])
+
+
 @pytest.mark.parametrize("layer", ["first", "last"])
 def test_mlp_split_layers_propagate_non_finite_values_as_float32(layer):
     """A row with an infinite or NaN input of a split layer (512 inputs) gives the infinities and NaN
