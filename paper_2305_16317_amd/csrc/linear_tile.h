@@ -26,16 +26,22 @@
 // rows went from 140 to 58 us, over 320 from 72 to 40, over 100 from 34 to 26 and
 // over one from 21.5 to 19.5 (row-major operands on fp32 MFMA before).
 //
-// Split products (SPLIT): a weight of feature n is held as 2^wexp[n] (w0 +
-// 2^-11 w1), two fp16 parts with the row's largest weight in [1, 2); an input
-// row x as x S = x0s + x1 in fp16 with S the power of two that puts the row's
-// largest value in [2^14, 2^15), and x0 = 2^-11 x0s.  w0 x0s + w0 x1 + w1 x0
-// then keeps about 22 bits of every product, and every fp16 product is exact
-// in the MFMA's fp32 accumulator: against float64 a forward of the policy is
-// 3.3e-7 off, 4.0e-7 with fp32 MFMA, at a fifth of the matrix time.  The row's
-// largest value comes from the producing layer, one maximum per row and
-// 16-feature tile (rmax); the first layer takes it from its own loads.  Layers
-// with few inputs and models with a non-finite weight run on fp32 MFMA.
+// Split products (SPLIT): a weight of feature n is held as 2^wexp[n] (w0 + w1),
+// two fp16 parts with the feature's largest weight in [2^14, 2^15); an input row
+// x as x S = x0 + x1 in fp16 with S = 2^-xexp the power of two that puts the
+// row's largest value in [2^14, 2^15).  w0 x0, and w0 x1 + w1 x0 in a sum of
+// their own (2^-11 as large, so that their roundings do not count), then keep
+// about 22 bits of every product of values within 2^-16 of the largest, and
+// 2^-39 of the largest below; w1 x1 is left out.  Every fp16 product is exact in
+// the MFMA's fp32 accumulator, and one such chunk of 32 inputs rounds the large sum
+// once: against float64 a forward of the policy is 2.5e-7 off, 4.0e-7 with fp32
+// MFMA and 3.2e-7 with one sum for all three products, at a fifth of the matrix
+// time.  What is left is the split of the weights, which stays the same along
+// a chain: with a third part, held exactly, 100-step samples were another 8 %
+// closer to float64, for half as much again to load (a forward of 1024 rows 98 us
+// for 80).  The row's largest value comes from the producing layer, one maximum
+// per row and 16-feature tile (rmax); the first layer takes it from its own loads.
+// Layers with few inputs and models with a non-finite weight run on fp32 MFMA.
 #pragma once
 
 #include "pd_internal.h"
@@ -114,7 +120,7 @@ struct LinearChunk {
 };
 
 struct SplitX {
-    lin_h8 x0s, x1, x0;
+    lin_h8 x0, x1;
 };
 __device__ __forceinline__ SplitX split_row(const lin_f4& a, const lin_f4& b, float S, bool nonfinite) {
     lin_u4 p0, p1;
@@ -132,17 +138,19 @@ __device__ __forceinline__ SplitX split_row(const lin_f4& a, const lin_f4& b, fl
         p1[q] = w;
     }
     SplitX s;
-    s.x0s = __builtin_bit_cast(lin_h8, p0);
+    s.x0 = __builtin_bit_cast(lin_h8, p0);
     s.x1 = __builtin_bit_cast(lin_h8, p1);
-    s.x0 = s.x0s * (_Float16)0.00048828125f;
     if (nonfinite) {
-        // an infinite or NaN input keeps its leading part only, so that its
-        // products are those of the value itself (a weight's leading part is
-        // zero only where the weight is)
+        // an infinite or NaN input goes to the second part alone, which meets
+        // only the weights' leading parts: its products are those of the value
+        // itself (a weight's leading part is zero only where the weight is)
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             const uint32_t bits = (p0[i >> 1] >> (16 * (i & 1))) & 0x7fff;
-            if (bits >= 0x7c00) s.x1[i] = s.x0[i] = (_Float16)0.f;
+            if (bits >= 0x7c00) {
+                s.x1[i] = s.x0[i];
+                s.x0[i] = (_Float16)0.f;
+            }
         }
     }
     return s;
@@ -206,9 +214,12 @@ __device__ __forceinline__ bool linear_tile(const LinearArgs& a, const TileRows&
         }
     }
 
-    // this lane's row of each row tile
+    // this lane's row of each row tile; in a hidden buffer the tile (the same
+    // pointer in every lane), the bytes from there to the row and those from one of
+    // its input groups of four to the next (32 and 24 bits: a width of 2^26 would
+    // have weights past any memory)
     const float* xp[RT];
-    int xs[RT];                                   // floats from one input group of four to the next
+    uint32_t xo[RT], xs[RT];
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
         const int row = min(16 * (mt0 + rt) + j, Mread - 1);
@@ -217,20 +228,19 @@ __device__ __forceinline__ bool linear_tile(const LinearArgs& a, const TileRows&
             const int gr = row / src.group, b = row % src.group;
             const int64_t sl = src.slot ? src.slot[gr] : gr;
             xp[rt] = src.base + sl * src.slot_stride + (int64_t)b * rows.D;
-            xs[rt] = 4;
         } else if constexpr (IN == IN_LDS) {
             xp[rt] = rows.x + j * rows.xs;
-            xs[rt] = 4;
         } else {
-            const int mt = row >> 4;
-            xp[rt] = rows.in.h + hidden_row(K, mt, row & 15);
-            xs[rt] = 4 * tile_rows(Mmax, mt);
+            const int mt = min(mt0 + rt, (Mmax - 1) >> 4);    // row / 16, the same in every lane
+            xp[rt] = rows.in.h + hidden_row(K, mt, 0);
+            xs[rt] = 16u * tile_rows(Mmax, mt);
+            xo[rt] = 16u * (row & 15);
         }
     }
     const lin_f4* wp[CT];
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct)
-        wp[ct] = static_cast<const lin_f4*>(a.w) + (int64_t)min(nt0 + ct, NT - 1) * KC * 128 + lane;
+        wp[ct] = static_cast<const lin_f4*>(a.w) + (int64_t)min(nt0 + ct, NT - 1) * KC * 128;
 
     const int per = (KC + kLinWaves - 1) / kLinWaves;
     const int c_begin = wave * per, c_end = min(c_begin + per, KC);
@@ -240,13 +250,17 @@ __device__ __forceinline__ bool linear_tile(const LinearArgs& a, const TileRows&
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
-            for (int q = 0; q < 2; ++q) ch.w[ct][q] = wp[ct][(int64_t)c * 128 + q * 64];
+            for (int q = 0; q < 2; ++q) ch.w[ct][q] = (wp[ct] + (int64_t)c * 128 + q * 64)[(uint32_t)lane];
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
             for (int q = 0; q < 2; ++q) {
                 const int k4 = min(8 * c + 4 * q + g, K4 - 1);
-                ch.x[rt][q] = *reinterpret_cast<const lin_f4*>(xp[rt] + (int64_t)k4 * xs[rt]);
+                if constexpr (IN == IN_HIDDEN)
+                    ch.x[rt][q] = *reinterpret_cast<const lin_f4*>(reinterpret_cast<const char*>(xp[rt]) +
+                                                                   (xo[rt] + __umul24(k4, xs[rt])));
+                else
+                    ch.x[rt][q] = *reinterpret_cast<const lin_f4*>(xp[rt] + 4 * (int64_t)k4);
             }
         return ch;
     };
@@ -271,7 +285,8 @@ __device__ __forceinline__ bool linear_tile(const LinearArgs& a, const TileRows&
 #pragma unroll
     for (int i = 0; i < E; ++i) {
         const int tile = min(2 * i + upper, RT * CT - 1);
-        const int n = min(16 * (nt0 + tile % CT) + on, N - 1);
+        // two feature tiles: the same one for all of a thread's outputs
+        const int n = min(16 * (nt0 + (CT == 2 ? upper : tile % CT)) + on, N - 1);
         const int row = min(16 * (mt0 + tile / CT) + oj, Mread - 1);
         if constexpr (GATHER) {
             const int gr = rows.src->group == 1 ? row : row / rows.src->group;
@@ -368,11 +383,12 @@ __device__ __forceinline__ bool linear_tile(const LinearArgs& a, const TileRows&
         }
     }
 
-    lin_f4 acc[RT][CT];
+    // split: the two small products have accumulators of their own (acl)
+    lin_f4 acc[RT][CT], acl[RT][CT];
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-        for (int ct = 0; ct < CT; ++ct) acc[rt][ct] = lin_f4{0.f, 0.f, 0.f, 0.f};
+        for (int ct = 0; ct < CT; ++ct) acc[rt][ct] = acl[rt][ct] = lin_f4{0.f, 0.f, 0.f, 0.f};
     auto compute = [&](Chunk& ch, int c) {
         if (8 * c + 8 > K4) {                                 // inputs past K (the last chunk of a ragged K)
 #pragma unroll
@@ -388,10 +404,13 @@ __device__ __forceinline__ bool linear_tile(const LinearArgs& a, const TileRows&
 #pragma unroll
                 for (int p = 0; p < 3; ++p)
 #pragma unroll
-                    for (int ct = 0; ct < CT; ++ct)
-                        acc[rt][ct] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
-                            __builtin_bit_cast(lin_h8, ch.w[ct][p == 2 ? 1 : 0]), p == 0 ? s.x0s : p == 1 ? s.x1 : s.x0,
-                            acc[rt][ct], 0, 0, 0);
+                    for (int ct = 0; ct < CT; ++ct) {
+                        // the main product between the two small ones, so that
+                        // none waits for the one before
+                        lin_f4& to = p == 1 ? acc[rt][ct] : acl[rt][ct];
+                        to = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(lin_h8, ch.w[ct][p == 2 ? 1 : 0]),
+                                                                    p == 0 ? s.x1 : s.x0, to, 0, 0, 0);
+                    }
             } else {
 #pragma unroll
                 for (int u = 0; u < 8; ++u)
@@ -421,7 +440,8 @@ __device__ __forceinline__ bool linear_tile(const LinearArgs& a, const TileRows&
     for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct)
-            *reinterpret_cast<lin_f4*>(&lds.part[wave][rt * CT + ct][4 * lane]) = acc[rt][ct];
+            *reinterpret_cast<lin_f4*>(&lds.part[wave][rt * CT + ct][4 * lane]) =
+                SPLIT ? acc[rt][ct] + acl[rt][ct] : acc[rt][ct];
     lds_barrier();
 #pragma unroll
     for (int i = 0; i < E; ++i) {

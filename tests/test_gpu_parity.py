@@ -166,6 +166,21 @@ def test_mlp_non_finite_weights_and_rows(layer):
     assert not np.isfinite(got[7]).any() and np.array_equal(got[keep], clean[keep])
 
 
+def test_mlp_split_products_are_closer_to_float64_than_float32():
+    """The policy network (all its products but the first layer's split).  The small products of a
+    split have sums of their own, so a 32-input chunk adds one rounding to the large sum and not
+    three: 2.5e-7 from float64, where fp32 products gave 4.0e-7 and one sum for all 3.2e-7."""
+    wl = _wl("mlp", (160,), 1024)
+    w = W.make_weights(wl.model)
+    rng = np.random.default_rng(6)
+    x = rng.standard_normal((300, 160)).astype(np.float32)
+    n = rng.integers(0, 100, 300).astype(np.int32)
+    tb = schedule.from_spec(wl.schedule)
+    ref = denoisers.Denoiser(wl.model, w, tb.alphabar, np.float64, False)(x.astype(np.float64), n)
+    rel = _rel(_forward(wl, w, x, n), ref)
+    assert rel <= 2.9e-7, rel
+
+
 def _value_class(a):
     return np.where(np.isnan(a), 2, np.where(np.isinf(a), np.sign(a), 0)).astype(int)
 
