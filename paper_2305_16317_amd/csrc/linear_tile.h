@@ -342,7 +342,8 @@ __device__ __forceinline__ bool linear_tile(const LinearArgs& a, const TileRows&
                 m[rt] = lds.mx[0][16 * rt + j];
 #pragma unroll
                 for (int v = 1; v < kLinWaves; ++v) m[rt] = umax32(m[rt], lds.mx[v][16 * rt + j]);
-                nonfinite |= m[rt] >= 0x7f800000u;
+                // (rows past the active ones may never have been written)
+                nonfinite |= m[rt] >= 0x7f800000u && 16 * (mt0 + rt) + j < M;
             }
         };
         all_waves();
