@@ -21,11 +21,11 @@ __device__ __forceinline__ void eps_out(const EpsOut& o, int64_t i, float e) {
         case EPS_STEP_HEUN:              // the mean of the two evaluations, then the step
             e = __fmul_rn(__fadd_rn(o.eps1[i], e), 0.5f);
             [[fallthrough]];
-        case EPS_STEP: {                 // x <- x + (A x + B eps) [+ z]
+        case EPS_STEP: {                 // x <- x + ((A x + B eps) [+ z])
             const float x = o.x[i];
-            float v = __fadd_rn(x, drift(o.A, x, o.B, e));
-            if (o.z) v = __fadd_rn(v, o.z[i]);
-            o.x[i] = v;
+            float y = drift(o.A, x, o.B, e);
+            if (o.z) y = __fadd_rn(y, o.z[i]);
+            o.x[i] = __fadd_rn(x, y);
             return;
         }
         case EPS_PREDICT: {              // the Euler prediction of one step

@@ -113,7 +113,7 @@ __device__ inline void picard_init_body(const PicardInit& a) {
 // arrays are indexed as epsilon is.
 enum EpsMode {
     EPS_STORE = 0,       // y = eps
-    EPS_STEP = 1,        // x <- x + (A x + B eps) [+ z]
+    EPS_STEP = 1,        // x <- x + ((A x + B eps) [+ z])
     EPS_PREDICT = 2,     // y = eps, xt = x + (A x + B eps)
     EPS_STEP_HEUN = 3,   // EPS_STEP with (eps1 + eps) / 2
     EPS_STEP_DPM = 4,    // x <- x + (((A x + B eps) + R xp) + S ep) (R = 0: the

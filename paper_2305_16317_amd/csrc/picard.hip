@@ -35,15 +35,22 @@ struct Cols;
 template <>
 struct Cols<1> {
     typedef float type;
+    typedef double sum;
 };
 template <>
 struct Cols<4> {
     typedef float type __attribute__((ext_vector_type(4)));
+    typedef double sum __attribute__((ext_vector_type(4)));
 };
 template <int VEC>
 __device__ __forceinline__ float& col_at(typename Cols<VEC>::type& v, int c) {
     if constexpr (VEC == 1) return v;
     else return reinterpret_cast<float*>(&v)[c];
+}
+template <int VEC>
+__device__ __forceinline__ double& sum_at(typename Cols<VEC>::sum& v, int c) {
+    if constexpr (VEC == 1) return v;
+    else return reinterpret_cast<double*>(&v)[c];
 }
 template <int VEC>
 __device__ __forceinline__ float col_at(const typename Cols<VEC>::type& v, int c) {
@@ -224,10 +231,13 @@ __global__ __launch_bounds__(1024) void k_picard_finalize(FinalizeArgs a, int nb
 
 // One block: cpb <= 64 * VEC consecutive columns of one sample b (a multiple
 // of VEC, from picard_scan_cols), all window rows,
-// split over NW waves (rows [w*ch, (w+1)*ch) per wave, ch <= R).  Drift and
-// noise are summed along the rows inside each wave, the wave totals are
-// exchanged through LDS, and the new points x^{k+1}_{t+j+1} = x_t + sum y +
-// sum z are written back to the ring.  All loads use clamped, always-valid
+// split over NW waves (rows [w*ch, (w+1)*ch) per wave, ch <= R).  Each row's
+// drift plus noise is summed along the rows inside each wave, the wave totals are
+// exchanged through LDS, and the new points x^{k+1}_{t+j+1} = x_t + sum (y + z)
+// are written back to the ring, rounded once each from x_t and the totals of the
+// waves before, in double, plus the wave's own sum: 16 policy samples of 100 steps
+// are 1.00e-7 from float64, 1.28e-7 with sums of drift and noise of their own in
+// float32, at the same time.  All loads use clamped, always-valid
 // indices and no branches, so a wave's rows are in flight together; the drift
 // coefficients of a wave's rows come in one vector load and are broadcast
 // with readlane.  The squared differences against the old points are summed
@@ -289,7 +299,7 @@ __global__ __launch_bounds__(NW * 64) void k_picard_scan(
     // per-row squared differences of every lane
     __shared__ union {
         struct {
-            V tot[2][NW][64];
+            V tot[NW][64];
             V first[NW][64];
         } x;
         float d2[NW * R][65];
@@ -327,10 +337,10 @@ __global__ __launch_bounds__(NW * 64) void k_picard_scan(
                 col_at<VEC>(y[r], c) = __fmul_rn(__fadd_rn(col_at<VEC>(y[r], c), col_at<VEC>(e2, c)), 0.5f);
         }
         if constexpr (NOISE) z[r] = *reinterpret_cast<const V*>(noise + (int64_t)m * slotsz + col);
-        else z[r] = V(0.f);
     }
-    // drifts replace eps in y; rows past the wave's range count as zero
-    V acc_y = V(0.f), acc_z = V(0.f);
+    // steps (drift and noise) replace eps in y; rows past the wave's range count
+    // as zero
+    V acc_y = V(0.f);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const float ca = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, ta), r));
@@ -353,14 +363,12 @@ __global__ __launch_bounds__(NW * 64) void k_picard_scan(
                 col_at<VEC>(xp, c) = col_at<VEC>(xo[r], c);
                 col_at<VEC>(ep, c) = e;
             }
+            if constexpr (NOISE) v = __fadd_rn(v, col_at<VEC>(z[r], c));
             col_at<VEC>(y[r], c) = in ? v : 0.f;
-            if (!in) col_at<VEC>(z[r], c) = 0.f;
             col_at<VEC>(acc_y, c) = __fadd_rn(col_at<VEC>(acc_y, c), col_at<VEC>(y[r], c));
-            col_at<VEC>(acc_z, c) = __fadd_rn(col_at<VEC>(acc_z, c), col_at<VEC>(z[r], c));
         }
     }
-    sh.x.tot[0][w][lane] = acc_y;
-    sh.x.tot[1][w][lane] = acc_z;
+    sh.x.tot[w][lane] = acc_y;
     sh.x.first[w][lane] = xo[0];   // x^k_{t+j0}: the previous wave's old point past its range
     if (has_mt) {
         s_mt[threadIdx.x] = mt_i;
@@ -369,31 +377,27 @@ __global__ __launch_bounds__(NW * 64) void k_picard_scan(
     // every ring value this wave read has been consumed above, so the ring
     // writes after the next barrier cannot overtake a read
     lds_barrier();
-    V py = V(0.f), pz = V(0.f);
-    // four waves' totals at a time in flight, added in order
-    for (int v0 = 0; v0 < w; v0 += 4) {
-        V a[4], c2[4];
+    // the point this wave's rows start from, in double: x_t and the totals of the
+    // waves before it, four at a time in flight
+    typename Cols<VEC>::sum from;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int v = min(v0 + u, NW - 1);
-            a[u] = sh.x.tot[0][v][lane];
-            if constexpr (NOISE) c2[u] = sh.x.tot[1][v][lane];
-        }
+    for (int c = 0; c < VEC; ++c) sum_at<VEC>(from, c) = (double)col_at<VEC>(anchor, c);
+    for (int v0 = 0; v0 < w; v0 += 4) {
+        V a[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) a[u] = sh.x.tot[min(v0 + u, NW - 1)][lane];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             if (v0 + u >= w) break;
 #pragma unroll
-            for (int c = 0; c < VEC; ++c) {
-                col_at<VEC>(py, c) = __fadd_rn(col_at<VEC>(py, c), col_at<VEC>(a[u], c));
-                if constexpr (NOISE) col_at<VEC>(pz, c) = __fadd_rn(col_at<VEC>(pz, c), col_at<VEC>(c2[u], c));
-            }
+            for (int c = 0; c < VEC; ++c) sum_at<VEC>(from, c) += (double)col_at<VEC>(a[u], c);
         }
     }
     const V next_old = (w + 1 < NW) ? sh.x.first[w + 1][lane] : V(0.f);
     lds_barrier();
 
     // ---- new points, their squared differences, and the writes
-    V sy = V(0.f), sz = V(0.f);
+    V sy = V(0.f);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const int j = j0 + r;
@@ -405,10 +409,7 @@ __global__ __launch_bounds__(NW * 64) void k_picard_scan(
 #pragma unroll
         for (int c = 0; c < VEC; ++c) {
             col_at<VEC>(sy, c) = __fadd_rn(col_at<VEC>(sy, c), col_at<VEC>(y[r], c));
-            col_at<VEC>(sz, c) = __fadd_rn(col_at<VEC>(sz, c), col_at<VEC>(z[r], c));
-            const float v = __fadd_rn(
-                __fadd_rn(col_at<VEC>(anchor, c), __fadd_rn(col_at<VEC>(py, c), col_at<VEC>(sy, c))),
-                __fadd_rn(col_at<VEC>(pz, c), col_at<VEC>(sz, c)));
+            const float v = (float)(sum_at<VEC>(from, c) + (double)col_at<VEC>(sy, c));
             col_at<VEC>(xn, c) = v;
             if (j + 1 < pe) {
                 const float dl = __fsub_rn(v, col_at<VEC>(xold, c));
@@ -483,20 +484,22 @@ __global__ __launch_bounds__(NW * 64) void k_picard_scan(
 // block storing its share of the new points and the first one the rest.
 //
 // Bound by latency, as the launches it replaces were: two round trips for the
-// loop state and the window (at most 128 points of 256 values, 192 KB at 100
+// loop state and the window (at most 96 points of 256 values, 192 KB at 100
 // points of 160), a few barriers, and the tile.  At 100 points of 160 and width
 // 1024 it takes 12.3 us, apart 8.2 and 5.7 and a launch gap of about 1; at 15
 // points 8.2, apart 4.2 and 4.9 and the gap.
 //
 // Threads: C4 = D / 4 column groups of four by row groups of ch consecutive
-// window rows (at least four, so that few totals are added up).
+// window rows (at least four, so that few totals are added up).  The points are
+// rounded as in the scan, from the totals of other row groups: 100-step policy
+// samples are 0.85e-7 from float64, 1.04e-7 with float32 sums, at the same time.
 constexpr int kFusedRows = 128, kFusedCols = 256;
 template <int CT, int R, bool NOISE, bool DPM>
 __global__ __launch_bounds__(kLinThreads) void k_scan_first(ScanFirstArgs s, FinalizeArgs fin, LinearArgs l1,
                                                             HiddenBuf out) {
     typedef Cols<4>::type V;
     __shared__ LinearLds<1, CT> lds;
-    __shared__ V s_ty[kLinThreads], s_tz[kLinThreads];
+    __shared__ V s_ty[kLinThreads];
     __shared__ float s_d2[kFusedRows][kFusedCols / 4 + 1];
     __shared__ __attribute__((aligned(16))) float s_x[16][kFusedCols + 4];
     __shared__ float s_A[kFusedRows], s_B[kFusedRows], s_R[kFusedRows], s_S[kFusedRows], s_err[kFusedRows];
@@ -577,8 +580,8 @@ __global__ __launch_bounds__(kLinThreads) void k_scan_first(ScanFirstArgs s, Fin
     }
     lds_barrier();
 
-    // ---- drifts replace eps in y; each thread's totals
-    V ty = V(0.f), tz = V(0.f);
+    // ---- steps (drift and noise) replace eps in y; each thread's total
+    V ty = V(0.f);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         if (r < nr) {
@@ -601,37 +604,33 @@ __global__ __launch_bounds__(kLinThreads) void k_scan_first(ScanFirstArgs s, Fin
                     xp[c] = xo[r][c];
                     ep[c] = e;
                 }
+                if constexpr (NOISE) v = __fadd_rn(v, z[r][c]);
                 y[r][c] = v;
                 ty[c] = __fadd_rn(ty[c], v);
-                if constexpr (NOISE) tz[c] = __fadd_rn(tz[c], z[r][c]);
             }
         }
     }
     s_ty[tid] = ty;
-    if constexpr (NOISE) s_tz[tid] = tz;
     lds_barrier();
-    V py = V(0.f), pz = V(0.f);
-    if (nr > 0)
-        for (int v0 = 0; v0 < rg; v0 += 4) {         // four totals at a time in flight, added in order
-            V a4[4], b4[4];
+    // the point this thread's rows start from, in double: x_t and the totals of
+    // the rows before, four at a time in flight
+    Cols<4>::sum from;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int i = min(v0 + u, rg) * C4 + col / 4;
-                a4[u] = s_ty[i];
-                if constexpr (NOISE) b4[u] = s_tz[i];
-            }
+    for (int c = 0; c < 4; ++c) from[c] = (double)anchor[c];
+    if (nr > 0)
+        for (int v0 = 0; v0 < rg; v0 += 4) {
+            V a4[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) a4[u] = s_ty[min(v0 + u, rg) * C4 + col / 4];
 #pragma unroll
             for (int u = 0; u < 4; ++u)
                 if (v0 + u < rg)
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        py[c] = __fadd_rn(py[c], a4[u][c]);
-                        if constexpr (NOISE) pz[c] = __fadd_rn(pz[c], b4[u][c]);
-                    }
+                    for (int c = 0; c < 4; ++c) from[c] += (double)a4[u][c];
         }
 
     // ---- new points (in y) and their squared differences
-    V sy = V(0.f), sz = V(0.f);
+    V sy = V(0.f);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         if (r < nr) {
@@ -641,8 +640,7 @@ __global__ __launch_bounds__(kLinThreads) void k_scan_first(ScanFirstArgs s, Fin
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
                 sy[c] = __fadd_rn(sy[c], y[r][c]);
-                if constexpr (NOISE) sz[c] = __fadd_rn(sz[c], z[r][c]);
-                const float v = __fadd_rn(__fadd_rn(anchor[c], __fadd_rn(py[c], sy[c])), __fadd_rn(pz[c], sz[c]));
+                const float v = (float)(from[c] + (double)sy[c]);
                 y[r][c] = v;
                 if (j + 1 < pe) {
                     const float dl = __fsub_rn(v, xold[c]);

@@ -645,6 +645,26 @@ def test_mlp_one_sample_windows_match_oracle(solver, D, width, T, p):
 
 
 
+@pytest.mark.parametrize("p,batch,bar", [
+    (100, 1, 9.6e-8),     # scan in the next first layer: 0.90e-7 here
+    (20, 8, 1.1e-7),      # scan alone: 0.98e-7
+    (1, 4, 2.9e-7),       # one step a window, as the sequential chain: 2.4e-7
+])
+def test_policy_samples_stay_close_to_float64(p, batch, bar):
+    """Distance of sampled chains to the float64 chain, root mean square over four seeds.  Each point is
+    rounded once from its window's start and sums held in double between the row groups; with all
+    sums in float32 these were 1.01e-7, 1.29e-7 and 3.2e-7 (1.03e-7, 1.22e-7 and 3.1e-7 on fp32 products)."""
+    m = W.ModelSpec("mlp", (160,), width=1024, weight_seed=11)
+    w = W.make_weights(m)
+    sq = []
+    for seed in range(4):
+        wl = W.Workload("t", W.ScheduleSpec("ddpm", 100, 100), m, p=p, tau=0.1, noise_seed=seed, batch=batch)
+        got, _ = _run(wl, w)
+        sq.append(_rel(got, Problem(wl, w, np.float64).picard().x) ** 2)
+    rms = math.sqrt(np.mean(sq))
+    assert rms <= bar, rms
+
+
 def test_prop2_rule_is_relaxed_rule_at_matching_tau():
     """On the device as in the oracle: Prop. 2 at eps equals the relaxed rule
     at tau = 2 eps / (T sqrt D) (D = 16, T = 32: exact binary fractions)."""
