@@ -50,8 +50,13 @@ __device__ inline int row_timestep(const RowSrc& s, int64_t g) {
 
 // Loop state of one Picard run, in device memory.
 struct LoopState {
-    int32_t t;       // window start
-    int32_t k;       // iterations done
+    union {
+        struct {
+            int32_t t;   // window start
+            int32_t k;   // iterations done
+        };
+        uint64_t progress;   // both (t in the low half), for the host's copy
+    };
     int32_t f;       // frontier: highest trajectory index holding a computed point
     int32_t p_eff;   // size of the current window; 0 once t >= T or after an error
     int32_t status;  // PD_OK or PD_ERR_NUMERIC
@@ -62,12 +67,15 @@ struct LoopState {
 };
 // The host reads the loop state from a copy in mapped, coherent pinned host
 // memory that the kernels write as they change it (no copy launch per batch).
-// It reads it after an event or stream synchronisation, whose release makes the
-// stores visible: a system-scope fence here cost each iteration over 1 us.
+// t and k go in one 64-bit store and are read by one load, because the host reads
+// them after waiting for a batch's last iteration but one, while that last one
+// may be storing here.  The other fields count after a synchronisation alone,
+// whose release makes the stores visible (first_stride before it too: it stays as
+// the first iteration left it); a system-scope fence here cost each iteration
+// over 1 us.
 __device__ inline void mirror_state(const LoopState& v, LoopState* host) {
     if (!host) return;
-    host->t = v.t;
-    host->k = v.k;
+    __hip_atomic_store(&host->progress, v.progress, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     host->f = v.f;
     host->p_eff = v.p_eff;
     host->status = v.status;

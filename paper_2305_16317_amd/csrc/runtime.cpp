@@ -14,6 +14,7 @@
 #include "gmm.h"
 #include "mlp.h"
 #include "pd_internal.h"
+#include "picard_plan.h"
 
 namespace pd {
 
@@ -1055,43 +1056,15 @@ extern "C" pd_status pd_sample_picard(const pd_schedule* s, const pd_denoiser* d
         // previous batch's last iteration (it waits on an event recorded
         // before that iteration): the GPU never waits idle for the host.
         volatile LoopState* hs = w.h_state;
-        hs->t = 0;              // the copy still holds the previous call's end
-        hs->k = 0;
+        hs->progress = pack_progress(0, 0);   // the copy still holds the previous call's end
         hs->status = PD_OK;
         hs->first_stride = 0;
         int t_host = 0, k_host = 0, issued = 0;
+        bool drained = false;
         for (;;) {
-            // every iteration advances t by at most pc, so at least this many
-            // more are needed.  Beyond that, enqueue as many as the mean stride
-            // after the first predicts (the first window holds copies of x_0 and
-            // in practice slides by one), but at most as many as are already
-            // done: strides grow as the trajectory converges, so early means
-            // overestimate what is left, and iterations enqueued past the end
-            // (they find p_eff = 0 on the device and return at once) still cost
-            // a dispatch each.  Iterations still queued count against it.
-            // The first batch adds one iteration more than the first window's
-            // slide of one requires: the host then decides the second batch
-            // from two finished iterations (the mean stride) while a third
-            // still runs, instead of draining the stream and leaving the GPU
-            // idle; it is wasted only when the loop ends within two iterations.
-            const int in_flight = issued - k_host;
-            int need = (T - t_host + pc - 1) / pc;
-            if (issued == 0 && T > 1) need = 2 + (T - 1 + pc - 1) / pc;
-            const int first_stride = hs->first_stride;
-            if (k_host >= 2 && t_host > first_stride) {
-                const double mean = (double)(t_host - first_stride) / (double)(k_host - 1);
-                int est = (int)std::ceil((double)(T - t_host) / mean);
-                est = est < issued ? est : issued;
-                need = need > est ? need : est;
-            }
-            // the chain's last point (sigma = 0) is held to no change at all and so
-            // takes an iteration of its own: while more than that point is left,
-            // one in flight does not end the loop
-            if (need <= in_flight && T - t_host > 1) need = in_flight + 1;
-            need = need < T - t_host ? need : T - t_host;   // stride >= 1 bounds the rest
-            need -= in_flight;
-            if (issued + need > T) need = T - issued;
-            if (need > 0) {
+            const PicardPlan plan = picard_plan(T, pc, issued, t_host, k_host, hs->first_stride, drained);
+            const int need = plan.n;
+            if (plan.next == PicardNext::QUEUE) {
                 tm.mark(-1);
                 for (int it = 0; it < need; ++it) {
                     const bool last = it == need - 1;
@@ -1129,21 +1102,25 @@ extern "C" pd_status pd_sample_picard(const pd_schedule* s, const pd_denoiser* d
                     else launch_scan();
                 }
                 issued += need;
+                drained = false;
                 // every iteration but the batch's last has run: decide the
                 // next batch while that one runs
                 PD_HIP(hipEventSynchronize(w.batch_event));
-            } else if (in_flight > 0) {
-                // the queued ones may finish the loop
+            } else if (plan.next == PicardNext::DRAIN) {
                 if (open) {                         // the last one's scan is not queued yet
                     tm.mark(-1);
                     launch_scan_and_first();
                 }
                 PD_HIP(hipStreamSynchronize(st));
+                drained = true;
             } else {
                 fail(PD_ERR_DEVICE, "Picard loop did not terminate within T iterations");
             }
-            k_host = hs->k;
-            t_host = hs->t;
+            // one load of both: where the batch's last iteration has its scan
+            // queued too, it may be changing them now
+            const uint64_t now = __atomic_load_n(&w.h_state->progress, __ATOMIC_RELAXED);
+            k_host = progress_k(now);
+            t_host = progress_t(now);
             if (t_host >= T || hs->status != PD_OK) break;
         }
         PD_HIP(hipStreamSynchronize(st));     // every queued launch (the last wrote x_T out)
