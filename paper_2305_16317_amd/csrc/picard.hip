@@ -704,7 +704,9 @@ __global__ __launch_bounds__(kLinThreads) void k_scan_first(ScanFirstArgs s, Fin
             if (i >= 0 && i < 16) *reinterpret_cast<V*>(&s_x[i][col]) = y[r];
             if (j == pe - 1) {                       // points past the window's last repeat it
                 for (i = max(i + 1, 0); i < 16; ++i) *reinterpret_cast<V*>(&s_x[i][col]) = y[r];
-                if (bid == 0 && !bad && tn >= T) *reinterpret_cast<V*>(fin.x_out + col) = y[r];
+                if (bid == 0 && !bad && tn >= T)     // a caller's pointer: aligned to a float
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) fin.x_out[col + c] = y[r][c];
             }
         }
     }

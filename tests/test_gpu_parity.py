@@ -665,6 +665,30 @@ def test_policy_samples_stay_close_to_float64(p, batch, bar):
     assert rms <= bar, rms
 
 
+@pytest.mark.parametrize("kind,shape,width,batch", [
+    ("mlp", (20,), 32, 1), ("mlp", (20,), 32, 3), ("mlp", (260,), 32, 1), ("conv1x1", (4, 6, 7), 32, 1), ("gmm2d", (2,), 0, 2)])
+def test_sample_goes_to_any_float_address(kind, shape, width, batch):
+    """x_out one float past an aligned address: the same bits there, and nothing before or after."""
+    if kind == "gmm2d":
+        wl = W.small_variant("gmm2d_ddpm100", T=20, p=8, batch=batch)
+    else:
+        m = W.ModelSpec(kind, shape, width=width, weight_seed=3)
+        wl = W.Workload("t", W.ScheduleSpec("ddpm", 20, 20), m, p=8, tau=0.1, batch=batch)
+    w = W.make_weights(wl.model)
+    sched, den = pd.from_workload(wl, w)
+    n = wl.batch * wl.model.D
+    for sampler in ("picard", "sequential"):
+        want, _ = _run(wl, w, sampler)
+        buf = torch.full((n + 2,), 7.0, device="cuda")
+        if sampler == "picard":
+            pd.pd_sample_picard(sched, den, wl.p, wl.tau, wl.noise_seed, wl.batch, wl.model.sample_shape, buf[1:n + 1])
+        else:
+            pd.pd_sample_sequential(sched, den, wl.noise_seed, wl.batch, wl.model.sample_shape, buf[1:n + 1])
+        got = buf.cpu().numpy()
+        assert got[0] == 7.0 and got[n + 1] == 7.0
+        assert np.array_equal(got[1:n + 1], want.reshape(-1)), sampler
+
+
 def test_prop2_rule_is_relaxed_rule_at_matching_tau():
     """On the device as in the oracle: Prop. 2 at eps equals the relaxed rule
     at tau = 2 eps / (T sqrt D) (D = 16, T = 32: exact binary fractions)."""
