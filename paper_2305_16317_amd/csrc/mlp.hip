@@ -58,8 +58,6 @@ void k_linear_out(LinearArgs a, RowSrc src, HiddenBuf in, HeunPredictArgs h, Eps
 // 16 features; with `split`, also the exponent of each feature's power of two.  *nonfinite is
 // set when a weight is infinite or NaN.  Bound by the latency of its loads: whole
 // rows in 16-byte pieces, several in flight, 11 us for a layer of 1024 x 1024.
-// Creating a 160-1024-1024-1024-160 denoiser takes 1.39 ms, 1.43 with single
-// floats 4 KB apart, and the copies alone 1.32.
 __global__ __launch_bounds__(256) void k_pack_linear(const float* __restrict__ W, int N, int K, int split,
                                                      float* __restrict__ out, int32_t* __restrict__ wexp,
                                                      int32_t* nonfinite) {

@@ -114,6 +114,7 @@ def test_mlp_forward(shape, width, M):
     (4, 4, 1.0),          # one chunk, one feature tile, mostly padding
     (1100, 64, 1.0),      # a split first layer of more chunks than are held at once
     (520, 516, 1.0),      # split first layer, ragged
+    (2400, 64, 1.0),      # weights larger than the forward scratch they are packed through
 ])
 def test_mlp_tiles_match_float64(D, width, scale):
     """Every tile shape (row counts around its edges), against float64: a float32 evaluation
