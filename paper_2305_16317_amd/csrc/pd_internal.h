@@ -69,13 +69,14 @@ struct LoopState {
 // memory that the kernels write as they change it (no copy launch per batch).
 // t and k go in one 64-bit store and are read by one load, because the host reads
 // them after waiting for a batch's last iteration but one, while that last one
-// may be storing here.  The other fields count after a synchronisation alone,
+// may be storing here.  (Atomic so that it stays one store; a wider scope than a
+// wave's would wait for the host's memory, 0.3 us an iteration.)  The other fields count after a synchronisation alone,
 // whose release makes the stores visible (first_stride before it too: it stays as
 // the first iteration left it); a system-scope fence here cost each iteration
 // over 1 us.
 __device__ inline void mirror_state(const LoopState& v, LoopState* host) {
     if (!host) return;
-    __hip_atomic_store(&host->progress, v.progress, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(&host->progress, v.progress, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
     host->f = v.f;
     host->p_eff = v.p_eff;
     host->status = v.status;
