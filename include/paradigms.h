@@ -256,14 +256,15 @@ typedef struct pd_sample_stats {
     int32_t time_kernels;      /* in: nonzero = bracket every denoiser, update and     */
                                /*     finalize launch with HIP events on `stream`      */
     int32_t denoiser_launches; /* out (with time_kernels): denoiser calls timed        */
-    int32_t update_launches;   /* out: Picard update (scan) launches (sequential: 0, the
-                                  step is the denoiser's epilogue)                  */
+    int32_t update_launches;   /* out: Picard update (scan) or sequential step launches */
     int32_t finalize_launches; /* out: stride/slide launches (Picard only)             */
     double denoiser_ms;        /* out: summed event time of the denoiser calls         */
     double update_ms;          /* out: summed event time of the update launches        */
     double finalize_ms;        /* out: summed event time of the finalize launches      */
 } pd_sample_stats;
-/* When one block holds a sample's window (one sample of up to 256 values) the
+/* With time_kernels the sequential sampler's step is a launch of its own, with the
+ * same results (otherwise it runs in the denoiser's last launch).
+ * When one block holds a sample's window (one sample of up to 256 values) the
  * update launch also takes the stride and slides, and finalize_launches is 0; for
  * one MLP sample it also runs the next iteration's first layer, where the window
  * fits (up to 96 points of 256 values, 128 of 160 or fewer).

@@ -146,6 +146,8 @@ inline EpsOut eps_store(float* y) {
 }
 
 // ---------------------------------------------------------------- kernels
+// picard.hip: the same step as a launch of its own, on n stored epsilons
+void launch_eps_step(const EpsOut& out, const float* eps, int64_t n, hipStream_t s);
 // rng.hip
 void launch_normals(uint64_t seed, uint32_t rng_stream, int64_t count, float* out, hipStream_t s);
 // A sample's up-front draws in one launch: the prior x_0 (counter stream 0, BD

@@ -102,6 +102,12 @@ __global__ __launch_bounds__(256) void k_heun_predict(const LoopState* __restric
     }
 }
 
+// The sequential sampler's step apart from the denoiser: a run with timed
+// launches reports the two by themselves.
+__global__ __launch_bounds__(256) void k_eps_step(EpsOut out, const float* __restrict__ eps, int64_t n) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+        eps_out(out, i, eps[i]);
+}
 
 // The stride is known: record it, slide the window and write the next
 // iteration's row descriptors.  cur is the loop state as the iteration found
@@ -757,6 +763,11 @@ void launch_heun_predict(const LoopState* st, const float* ring, const float* ep
                          const float* B, int p, int64_t BD, float* xt, hipStream_t s) {
     hipLaunchKernelGGL(k_heun_predict, dim3(stream_blocks((int64_t)p * BD)), dim3(256), 0, s, st,
                        ring, eps, A, B, p, BD, xt);
+    PD_HIP(hipGetLastError());
+}
+
+void launch_eps_step(const EpsOut& out, const float* eps, int64_t n, hipStream_t s) {
+    hipLaunchKernelGGL(k_eps_step, dim3(stream_blocks(n)), dim3(256), 0, s, out, eps, n);
     PD_HIP(hipGetLastError());
 }
 

@@ -978,3 +978,20 @@ def test_multistep_and_heun_workspace_reuse(name, table):
         torch.cuda.synchronize()
         assert np.array_equal(x.cpu().numpy().reshape(wl.batch, -1).view(np.uint32),
                               seq_ref.view(np.uint32)), seed
+
+
+@pytest.mark.parametrize("name", ["mlp_small", "conv_ddpm", "conv_ddim_eta", "heun_gmm", "heun_mlp",
+                                  "heun_conv", "dpm_gmm", "dpm_conv"])
+def test_timed_sequential_launches_report_the_step_by_itself(name):
+    """With timed launches every step is one denoiser and one update interval, and the sample is the
+    untimed run's bit for bit."""
+    wl = {**SMALL, **HEUN, **DPM}[name]()
+    w = W.make_weights(wl.model)
+    ref, _ = _run(wl, w, "sequential")
+    sched, den = pd.from_workload(wl, w)
+    x = torch.empty(wl.batch * wl.model.D, device="cuda")
+    st = pd.pd_sample_sequential(sched, den, wl.noise_seed, wl.batch, wl.model.sample_shape, x, time_kernels=True)
+    k, T = st.kernel_times, wl.schedule.T
+    assert (k["denoiser_launches"], k["update_launches"], k["finalize_launches"]) == (T, T, 0)
+    assert k["denoiser_ms"] > 0.0 and k["update_ms"] > 0.0
+    assert np.array_equal(x.cpu().numpy().reshape(wl.batch, -1).view(np.uint32), ref.view(np.uint32))
