@@ -540,7 +540,7 @@ def test_picard_matches_oracle(name):
 
 
 @pytest.mark.parametrize("name", ["gmm_p7_b3", "gmm_k12", "gmm_k40", "mlp_small", "conv_ddpm",
-                                  "conv_ddim_b3", "conv_T1", "gmm_T2", "conv_ddim_eta"])
+                                  "conv_ddim_b3", "conv_T1", "gmm_T2", "conv_ddim_eta", "conv_cfg_f32"])
 def test_sequential_matches_oracle(name):
     wl = SMALL[name]()
     w = W.make_weights(wl.model)
@@ -550,7 +550,8 @@ def test_sequential_matches_oracle(name):
     assert _rel(got, ref) <= REL_F32
 
 
-@pytest.mark.parametrize("name", ["gmm_p7_b3", "gmm_k40", "gmm_ddim", "gmm_ddim_eta", "mlp_small", "conv_ddpm", "conv_ddim_b3"])
+@pytest.mark.parametrize("name", ["gmm_p7_b3", "gmm_k40", "gmm_ddim", "gmm_ddim_eta", "mlp_small", "conv_ddpm", "conv_ddim_b3",
+                                  "conv_cfg_f32"])
 def test_window_of_one_is_sequential_bitwise(name):
     wl = SMALL[name]()
     w = W.make_weights(wl.model)
@@ -995,3 +996,38 @@ def test_timed_sequential_launches_report_the_step_by_itself(name):
     assert (k["denoiser_launches"], k["update_launches"], k["finalize_launches"]) == (T, T, 0)
     assert k["denoiser_ms"] > 0.0 and k["update_ms"] > 0.0
     assert np.array_equal(x.cpu().numpy().reshape(wl.batch, -1).view(np.uint32), ref.view(np.uint32))
+
+
+# ------------------- the conv denoiser with the step in its last launch, guided and over several passes
+def _conv_chain(T, shape, width, batch=1, solver="euler", eta=0.0, guided=False, dtype="f32"):
+    spec = W.ScheduleSpec("ddim", 10 * T, T, eta=eta, solver=solver)
+    m = W.ModelSpec("conv1x1", shape, width=width, dtype=dtype, cond_dim=24 if guided else 0,
+                    guidance=3.0 if guided else 1.0)
+    return W.Workload("chain", spec, m, p=8, tau=0.1, batch=batch)
+
+
+@pytest.mark.parametrize("solver,eta", [("euler", 0.7), ("heun", 0.0), ("dpm2m", 0.0)])
+@pytest.mark.parametrize("shape,width,batch", [
+    ((4, 8, 8), 64, 2),         # one pass, some blocks without a tile for every wave
+    ((4, 96, 96), 32, 4),       # 2304 tiles: two passes, the next tile's x prefetched while x is rewritten
+])
+def test_guided_float32_steps_match_oracle_and_window_of_one(shape, width, batch, solver, eta):
+    wl = _conv_chain(8 if batch == 2 else 3, shape, width, batch, solver, eta, guided=True)
+    w = W.make_weights(wl.model)
+    seq, st = _run(wl, w, "sequential")
+    assert st.network_rows == 2 * batch * st.evals_per_sample
+    assert _rel(seq, Problem(wl, w, np.float32).sequential()) <= REL_F32
+    one, _ = _run(wl, w, "picard", p=1)
+    assert np.array_equal(one.view(np.uint32), seq.view(np.uint32))
+
+
+@pytest.mark.parametrize("solver,eta", [("euler", 0.0), ("euler", 0.7), ("heun", 0.0), ("dpm2m", 0.0)])
+@pytest.mark.parametrize("dtype,batch", [("f32", 4), ("bf16", 8)])   # 2304 tiles of 16 or of 32 pixels
+def test_steps_over_several_passes_are_the_window_of_one(dtype, batch, solver, eta):
+    wl = _conv_chain(4, (4, 96, 96), 32, batch, solver, eta, dtype=dtype)
+    w = W.make_weights(wl.model)
+    seq, _ = _run(wl, w, "sequential")
+    one, _ = _run(wl, w, "picard", p=1)
+    assert np.array_equal(one.view(np.uint32), seq.view(np.uint32))
+    if dtype == "f32":
+        assert _rel(seq, Problem(wl, w, np.float32).sequential()) <= REL_F32

@@ -69,3 +69,22 @@ def test_static_forward_rejects_rows_beyond_the_scratch():
     assert err.value.code == pd.PD_ERR_INVALID_ARG and "static scratch" in str(err.value)
     torch.cuda.synchronize()
     assert torch.all(e == 7.0)                       # nothing was launched
+
+
+@pytest.mark.parametrize("width", [4, 8, 20])
+def test_static_forward_at_the_most_rows_it_takes(width):
+    """Narrow networks: the row maxima beside the activations take the most room (as many words as
+    the activations at width 4), up to the last row that is accepted."""
+    model, sch = W.ModelSpec("mlp", (4,), width=width), W.ScheduleSpec("ddpm", 100, 100)
+    sched, den = pd.from_workload(W.Workload("t", sch, model, p=8, tau=0.1), W.make_weights(model))
+    M = (1 << 20) // (2 * width)
+    rng = np.random.default_rng(width)
+    x = torch.from_numpy(rng.standard_normal((M + 1, 4)).astype(np.float32)).cuda()
+    n = torch.from_numpy(rng.integers(0, 100, M + 1).astype(np.int32)).cuda()
+    ref, got = torch.empty((M, 4), device="cuda"), torch.empty((M, 4), device="cuda")
+    pd.pd_denoiser_forward(den, x[:M], n[:M], ref)
+    pd.pd_denoiser_forward_static(den, x[:M], n[:M], got)
+    torch.cuda.synchronize()
+    assert np.array_equal(got.cpu().numpy().view(np.uint32), ref.cpu().numpy().view(np.uint32))
+    with pytest.raises(pd.PdError):
+        pd.pd_denoiser_forward_static(den, x, n, torch.empty((M + 1, 4), device="cuda"))
