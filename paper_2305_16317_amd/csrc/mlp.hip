@@ -55,14 +55,20 @@ void k_linear_out(LinearArgs a, RowSrc src, HiddenBuf in, HeunPredictArgs h, Eps
 }
 
 // Weights [N][K] -> packed fragments (layout in linear_tile.h), one block per
-// 16 features; with `split`, also the exponent of each feature's power of two.  *nonfinite is
-// set when a weight is infinite or NaN.  Bound by the latency of its loads: whole
-// rows in 16-byte pieces, several in flight, 11 us for a layer of 1024 x 1024.
-__global__ __launch_bounds__(256) void k_pack_linear(const float* __restrict__ W, int N, int K, int split,
-                                                     float* __restrict__ out, int32_t* __restrict__ wexp,
-                                                     int32_t* nonfinite) {
+// 16 features and layer (blockIdx.y); with `split`, also the exponent of each
+// feature's power of two.  *nonfinite is set when a weight is infinite or NaN.
+// Bound by the latency of its loads: whole rows in 16-byte pieces, several in
+// flight, 11 us for a layer of 1024 x 1024, so that the layers go together.
+__global__ __launch_bounds__(256) void k_pack_linear(PackLayers layers, int32_t* nonfinite) {
     __shared__ uint32_t s_max[16];
+    const PackLayer& a = layers.at[blockIdx.y];
+    const float* __restrict__ W = a.w;
+    float* __restrict__ out = a.out;
+    int32_t* __restrict__ wexp = a.wexp;
+    const int N = a.N, K = a.K;
+    const bool split = wexp != nullptr;
     const int nt = blockIdx.x, tid = threadIdx.x, i = tid & 15;
+    if (16 * nt >= N) return;                    // uniform over the block
     const int n = 16 * nt + i;
     const lin_f4 zero = {0.f, 0.f, 0.f, 0.f};
     {   // 16 neighbouring threads a feature
@@ -217,10 +223,11 @@ HiddenBuf hidden_buf(float* p, int64_t rows, int width) {
 
 size_t packed_linear_floats(int N, int K) { return (size_t)((N + 15) / 16) * ((K + 31) / 32) * 512; }
 
-void launch_pack_linear(const float* W, int N, int K, float* out, int32_t* wexp, int32_t* nonfinite,
-                        hipStream_t s) {
-    hipLaunchKernelGGL(k_pack_linear, dim3((unsigned)((N + 15) / 16)), dim3(256), 0, s, W, N, K, wexp ? 1 : 0, out,
-                       wexp, nonfinite);
+void launch_pack_linear(const PackLayers& layers, int count, int32_t* nonfinite, hipStream_t s) {
+    int n = 0;
+    for (int i = 0; i < count; ++i) n = layers.at[i].N > n ? layers.at[i].N : n;
+    hipLaunchKernelGGL(k_pack_linear, dim3((unsigned)((n + 15) / 16), (unsigned)count), dim3(256), 0, s, layers,
+                       nonfinite);
     PD_HIP(hipGetLastError());
 }
 

@@ -208,10 +208,18 @@ struct HiddenBuf {
 size_t hidden_floats(int64_t rows, int width);           // floats of one buffer (a multiple of 4)
 HiddenBuf hidden_buf(float* p, int64_t rows, int width);
 size_t packed_linear_floats(int N, int K);
-// W [N][K] (device) -> out; split into fp16 parts when wexp is given.
+// w [N][K] (device) -> out; split into fp16 parts when wexp is given.
 // *nonfinite (device) is set when a weight is infinite or NaN.
-void launch_pack_linear(const float* W, int N, int K, float* out, int32_t* wexp, int32_t* nonfinite,
-                        hipStream_t s);
+struct PackLayer {
+    const float* w;
+    float* out;
+    int32_t* wexp;
+    int32_t N, K;
+};
+struct PackLayers {
+    PackLayer at[4];
+};
+void launch_pack_linear(const PackLayers& layers, int count, int32_t* nonfinite, hipStream_t s);
 // first layer (rows gathered from `src`, fp32 weights), a hidden layer, and the
 // last layer (no activation, row-major output).  Buffers are those of
 // max_groups * group rows.

@@ -424,11 +424,12 @@ struct pd_denoiser {
 // 2.6e-7 and 2.4e-7 at 256.  With an infinite or NaN weight the whole model
 // keeps fp32 weights, whose products propagate those as they are.
 static constexpr int kSplitInputs = 512;
-// The packing runs while the host works out the first layer's shifts: creating a
-// denoiser of 160-W-W-W-160 takes 229 us at W = 64, 422 at 256 and 1.24 ms at 1024;
-// with each layer's copy waiting for the one before to be packed, and the shifts
-// first, 265, 507 and 1.47.  Row-major weights, copied and not packed, took 234, 434
-// and 1.43.
+// The layers are packed by one launch while the host works out the first layer's
+// shifts: creating a denoiser of 160-W-W-W-160 takes 270 us at W = 128, 447 at 256
+// and 1.30 ms at 1024 with 100 timesteps, and 190, 296 and 721 us
+// with 15, where the shifts hide less (a split layer's flag is waited for).  Row-major weights, copied and not packed, took 284,
+// 461 and 1.42 ms, and 191, 288 and 717 us; a launch a layer, 279, 450 and 1.29 ms,
+// and 200, 305 and 714 us.
 struct MlpPacker {
     pd_denoiser& d;
     const float* w[4];
@@ -459,8 +460,11 @@ struct MlpPacker {
     void copy(int i, float* to) {              // copies and launches are ordered on the null stream
         PD_HIP(hipMemcpy(to, w[i], size[i] * sizeof(float), hipMemcpyHostToDevice));
     }
+    PackLayer layer(int i, const float* from) const {
+        return PackLayer{from, d.W[i].as<float>(), d.wexp[i], n[i], k[i]};
+    }
     void pack(int i, const float* from, int32_t* flag) {
-        launch_pack_linear(from, n[i], k[i], d.W[i].as<float>(), d.wexp[i], flag, nullptr);
+        launch_pack_linear(PackLayers{{layer(i, from)}}, 1, flag, nullptr);
     }
     void start(int32_t* flag) {
         for (int i = 0; i < 4; ++i) {
@@ -468,14 +472,15 @@ struct MlpPacker {
             d.W[i].alloc((packed + (size_t)n[i]) * sizeof(float));
             d.wexp[i] = k[i] >= kSplitInputs ? d.W[i].as<int32_t>() + packed : nullptr;
         }
-        size_t at = 0;
+        PackLayers layers;
+        float* at = raw;
         for (int i = 0; i < 4; ++i) {
-            copy(i, raw + at);
+            copy(i, at);
+            layers.at[i] = layer(i, at);
             if (together) at += size[i];
             else pack(i, raw, flag);
         }
-        at = 0;
-        for (int i = 0; together && i < 4; at += size[i++]) pack(i, raw + at, flag);
+        if (together) launch_pack_linear(layers, 4, flag, nullptr);
     }
     // after this nothing is queued any more
     void finish(int32_t* flag) {
