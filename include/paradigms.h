@@ -173,11 +173,15 @@ pd_status pd_schedule_multistep_tables(const pd_schedule* s, float* R, float* S)
  * fp32 ones).  Each weight is split into its nearest fp16 value and a
  * 2^11-scaled fp16 remainder, each activation likewise after a power-of-two
  * scale per tile of 16 pixels and layer, and three part products per
- * multiply-add leave an error of about one float32 rounding.  A conv1x1 weight of magnitude 65504 or more makes creation fail
- * with PD_ERR_UNSUPPORTED; non-finite activations propagate as in float32.
+ * multiply-add leave an error of about one float32 rounding.  A conv1x1 weight
+ * of magnitude 65504 or more makes creation fail with PD_ERR_UNSUPPORTED;
+ * non-finite activations propagate as in float32.
  * For the MLP a layer of 512 or more inputs runs in the same way, each weight
  * scaled by a power of two per output feature and each input by one per row
- * (finite weights of any magnitude), and a shorter one on the fp32 matrix cores.
+ * (finite weights of any magnitude), and a shorter one on the fp32 matrix
+ * cores.  Weights and inputs within 2^-16 of the largest of their feature or
+ * row keep about 22 bits; below, what is left out is 2^-39 of that largest,
+ * also where the largest itself meets a zero.
  * dtype PD_BF16 (conv1x1 only) rounds every matmul operand to bfloat16
  * (round to nearest even) and accumulates in float32.
  * The training schedule `train` supplies abar (GMM) and T_train (the range
@@ -208,8 +212,8 @@ void pd_denoiser_destroy(pd_denoiser* d);
 /* eps[m] = eps(x[m], model_t[m]) for m in [0, M) (the network evaluations of
  * Algorithm 1's drift step).  x, eps: device float [M][D]; model_t: device
  * int32 [M], each in [0, T_train); a value outside that range is clamped to
- * it (the network's tables hold only those timesteps).  Enqueued on `stream` of the denoiser's
- * device; x and eps must not overlap.  M = 0 is a no-op.  Allocates nothing:
+ * it (the network's tables hold only those timesteps).  Enqueued on `stream`
+ * of the denoiser's device; x and eps must not overlap.  M = 0 is a no-op.  Allocates nothing:
  * the MLP's hidden activations go through scratch the denoiser allocated at
  * creation (in chunks of 1024 rows), and calls on several threads or streams
  * are ordered on the device so that they never share it at once. */
@@ -222,11 +226,12 @@ pd_status pd_denoiser_forward(const pd_denoiser* d, const float* x, const int32_
  * event or lock; the launches on `stream` are all it does.  The MLP's hidden
  * activations (2 * width floats per row, and their row maxima) go to a static
  * device array (8.5 MiB) that each GPU holds until the process ends, with room
- * for 2^20 activations, so for the MLP M * 2 * width <= 2^20 (M <= 512 at width 1024); larger M returns
- * PD_ERR_INVALID_ARG.  The mixture and conv1x1 models use no scratch and take
- * any M.  Every call on one GPU shares that array: calls whose work overlaps
- * on the device (other streams, or host threads) race and give undefined
- * results; calls ordered on one stream are safe.  Each layer overwrites its
+ * for 2^20 activations, so for the MLP M * 2 * width <= 2^20 (M <= 512 at
+ * width 1024); larger M returns PD_ERR_INVALID_ARG.  The mixture and conv1x1
+ * models use no scratch and take any M.  Every call on one GPU shares that
+ * array: calls whose work overlaps on the device (other streams, or host
+ * threads) race and give undefined results; calls ordered on one stream are
+ * safe.  Each layer overwrites its
  * part before reading it, so nothing needs clearing between calls. */
 pd_status pd_denoiser_forward_static(const pd_denoiser* d, const float* x,
                                      const int32_t* model_t, int64_t M, float* eps,
@@ -277,10 +282,10 @@ typedef struct pd_workspace pd_workspace;
 
 /* Buffers for sampling with window p and batch size `batch` on the current
  * device: the window ring of p+1 points (p+2 for PD_DDIM_DPM2M, which also
- * keeps x_{t-1}; twice for one MLP sample of up to 256 values), the noise of all T steps, the drift batch and the loop
- * state, plus mapped pinned host memory that the kernels write the loop
- * state and the stride of every iteration into (so the host reads them
- * without copies).  Lets repeated calls avoid allocation. */
+ * keeps x_{t-1}; twice for one MLP sample of up to 256 values), the noise of
+ * all T steps, the drift batch and the loop state, plus mapped pinned host
+ * memory that the kernels write the loop state and the stride of every
+ * iteration into (so the host reads them without copies).  Lets repeated calls avoid allocation. */
 pd_status pd_workspace_create(const pd_schedule* s, const pd_denoiser* d, int32_t p,
                               int32_t batch, pd_workspace** out);
 void pd_workspace_destroy(pd_workspace* w);

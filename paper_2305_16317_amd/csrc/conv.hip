@@ -71,7 +71,7 @@ struct ConvKernArgs {
     RowSrc src;
     EpsOut eo;
     int tiles_per_row;
-    int per;             // tiles per block and pass (tiles_per_pass) of all the rows
+    int per;             // k_conv_f32s: tiles per block and pass (tiles_per_pass) of all the rows
 };
 __device__ __forceinline__ EpsOut late_eps_out() {
     typedef const __attribute__((address_space(4))) char* ConstPtr;
@@ -294,7 +294,7 @@ void k_conv_bf16(ConvKernArgs ka) {
                     if (br + 1 < nbranch) dma_shift(cur.n, br + 1);
                     else dma_shift(nxt.n, 0);
                 }
-                    f16v o2[2] = {f16v{}, f16v{}};
+                f16v o2[2] = {f16v{}, f16v{}};
                 static_for<NB>([&](auto bc) {
                     constexpr int b = decltype(bc)::value;
                     static_for<2>([&](auto gc) {
@@ -512,8 +512,7 @@ __device__ __forceinline__ uint32_t lds_addr(T* p) {
     return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) T*)p;
 }
 
-//
-// Few tiles: the block's waves take `per` tiles a pass, as few as spread the
+// k_conv_f32s with few tiles: the block's waves take `per` tiles a pass, as few as spread the
 // tiles over all the blocks in the same number of passes, and the waves
 // without one only copy weights.  A lone wave per SIMD runs its tile faster than
 // two that share the LDS: one 4x96x96 row (576 tiles) took 31.0 us on 72 compute
@@ -965,7 +964,7 @@ void launch_bf16_t(const ConvArgs& a, const RowSrc& src, const EpsOut& out, hipS
     int64_t blocks = (ntiles + kBf16Waves - 1) / kBf16Waves;   // persistent: two blocks per CU
     if (blocks > 2 * device_cus()) blocks = 2 * device_cus();
     const dim3 grid((unsigned)blocks), block(kBf16Waves * 64);
-    const ConvKernArgs ka{a, src, out, tiles_per_row, kBf16Waves};
+    const ConvKernArgs ka{a, src, out, tiles_per_row, 0};
     if (out.mode != EPS_STORE)
         hipLaunchKernelGGL((k_conv_bf16<NB, C, true>), grid, block, 0, s, ka);
     else

@@ -23,8 +23,8 @@
 // j + 16 g and register e, feature 4 g + e of row j: the hidden layout's own
 // four floats, so the next layer reads what this one stores.
 // On one MI355X a forward of the 160-1024-1024-1024-160 policy network over 777
-// rows went from 140 to 58 us, over 320 from 72 to 40, over 100 from 34 to 26 and
-// over one from 21.5 to 19.5 (row-major operands on fp32 MFMA before).
+// rows went from 140 to 60 us, over 320 from 72 to 41, over 100 from 34 to 26 and
+// over one from 21.5 to 20 (row-major operands on fp32 MFMA before).
 //
 // Split products (SPLIT): a weight of feature n is held as 2^wexp[n] (w0 + w1),
 // two fp16 parts with the feature's largest weight in [2^14, 2^15); an input row

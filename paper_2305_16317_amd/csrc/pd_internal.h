@@ -220,7 +220,7 @@ struct PackLayers {
     PackLayer at[4];
 };
 void launch_pack_linear(const PackLayers& layers, int count, int32_t* nonfinite, hipStream_t s);
-// first layer (rows gathered from `src`, fp32 weights), a hidden layer, and the
+// first layer (rows gathered from `src`), a hidden layer, and the
 // last layer (no activation, row-major output).  Buffers are those of
 // max_groups * group rows.
 void launch_linear_first(const LinearArgs& a, const RowSrc& src, int64_t D, const HiddenBuf& out, hipStream_t s);

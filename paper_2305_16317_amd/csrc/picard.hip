@@ -495,8 +495,8 @@ __global__ __launch_bounds__(NW * 64) void k_picard_scan(
 // Bound by latency, as the launches it replaces were: two round trips for the
 // loop state and the window (at most 96 points of 256 values, 192 KB at 100
 // points of 160), a few barriers, and the tile.  At 100 points of 160 and width
-// 1024 it takes 12.3 us, apart 8.2 and 5.7 and a launch gap of about 1; at 15
-// points 8.2, apart 4.2 and 4.9 and the gap.
+// 1024 it takes 11.6 us, apart 8.2 and 5.7 and a launch gap of about 1; at 15
+// points 7.9, apart 4.2 and 4.9 and the gap.
 //
 // Threads: C4 = D / 4 column groups of four by row groups of ch consecutive
 // window rows (at least four, so that few totals are added up).  The points are

@@ -417,19 +417,22 @@ struct pd_denoiser {
 };
 
 // Packed weights of the MLP's four layers, laid out on the device.  A layer of
-// kSplitInputs inputs or more is split into fp16 parts: there the split's own
-// rounding (half a unit of fp32 per operand) is less than what fp32 sums of that
-// length lose.  Error of a forward against float64, all layers split and all
-// on fp32 MFMA: 3.4e-7 and 4.2e-7 at width 1024, 2.9e-7 and 3.1e-7 at 512,
-// 2.6e-7 and 2.4e-7 at 256.  With an infinite or NaN weight the whole model
-// keeps fp32 weights, whose products propagate those as they are.
+// kSplitInputs inputs or more is split into fp16 parts.  From there on the two
+// take as long (100 and 1024 rows of 160-W-W-W-160: 20.8 and 40.4 us at W = 508 on
+// fp32 MFMA, split 22.3 and 39.2; from 1024 the split is far ahead), and the
+// split's sums lose less: a forward is 2.4e-7 from float64 at 512 and 2.5e-7 at
+// 1024, on fp32 MFMA 3.0e-7 and 4.0e-7.  Below, fp32 is faster (at 256 19.8 and
+// 28.7 us, split 21.5 and 31.5) and about as close (2.5e-7, split 2.3e-7).  With an
+// infinite or NaN weight the whole model keeps fp32 weights, whose products
+// propagate those as they are.
 static constexpr int kSplitInputs = 512;
 // The layers are packed by one launch while the host works out the first layer's
-// shifts: creating a denoiser of 160-W-W-W-160 takes 270 us at W = 128, 447 at 256
-// and 1.30 ms at 1024 with 100 timesteps, and 190, 296 and 721 us
-// with 15, where the shifts hide less (a split layer's flag is waited for).  Row-major weights, copied and not packed, took 284,
-// 461 and 1.42 ms, and 191, 288 and 717 us; a launch a layer, 279, 450 and 1.29 ms,
-// and 200, 305 and 714 us.
+// shifts (one a layer where their weights do not fit the forward scratch together,
+// as at 1024): creating a denoiser of 160-W-W-W-160 takes 270 us at W = 128, 447
+// at 256 and 1.30 ms at 1024 with 100 timesteps, and 190, 296 and 721 us with 15,
+// where the shifts hide less.  Row-major weights, copied and not packed, took 284,
+// 461 and 1.42 ms, and 191, 288 and 717 us.  At 512 inputs a flag for infinite
+// weights is waited for too: 705 and 407 us, row-major 730 and 385.
 struct MlpPacker {
     pd_denoiser& d;
     const float* w[4];
