@@ -350,7 +350,7 @@ __global__ __launch_bounds__(1024) void k_gmm_picard_loop(GmmLoopArgs a, int noi
         v.evals = evals;
         v.status = s_bad ? PD_ERR_NUMERIC : PD_OK;
         *a.st = v;
-        mirror_state(v, a.st_host);
+        if (a.st_host) *a.st_host = v;   // read after the stream was synchronised: no order needed
     }
 }
 
